@@ -12,10 +12,10 @@
 #include "mbscan.h"
 #include "scan_bwd.hpp"
 #include "scan_params.hpp"
+#include "scan_ring.hpp"
 #include "scan_rowwise.hpp"
 #include "scan_step.hpp"
 #include "scan_tiled.hpp"
-#include "scan_ts2.hpp"
 #include "verify_rank.hpp"
 
 namespace {
@@ -63,26 +63,30 @@ hipError_t fwd_rowwise(ScanParams &p, void *stream) {
                   stream);
 }
 
-// The tiled kernel takes dstate 16 with 16-byte aligned activation rows.
-bool tiled_ok(const ScanParams &p, int64_t N, int32_t in_dtype, int32_t out_dtype) {
-    // 32-bit lane offsets inside a wave's rows: (16 rows) x L x 4 bytes < 2^32
-    if (N != 16 || p.seqlen % 16 != 0 || p.seqlen >= (int64_t(1) << 25)) return false;
+// The ring kernel takes dstate 16: any length below 2^25 (32-bit lane offsets inside a
+// wave's rows: 16 rows x L x 4 bytes < 2^32) and any row alignment, with fewer than 2^30
+// eight-channel chains (it indexes them in 32 bits; with time segments, only shapes of a
+// few hundred chains are multiplied).
+bool ring_ok(const ScanParams &p, int64_t N) {
+    return N == 16 && p.seqlen < (int64_t(1) << 25) && p.batch * ((p.dim + 7) / 8) < (int64_t(1) << 30);
+}
+
+// The 16-timestep kernel takes the verify shape: one slice, 16-byte aligned rows (its
+// loads are wider), no checkpoints, the batch in the grid's second dimension.
+bool short_ok(const ScanParams &p) {
     const void *ptrs[] = {p.u, p.delta, p.z, p.Bm, p.Cm, p.y};
     for (const void *q : ptrs)
         if (q && !aligned(q, 16)) return false;
-    (void)in_dtype; (void)out_dtype;
-    // fewer than 2^30 eight-channel waves: the kernel indexes its waves in 32 bits
-    // (with time segments, only shapes of a few thousand waves are multiplied)
-    return p.batch * ((p.dim + 7) / 8) < (int64_t(1) << 30);
+    return p.seqlen == 16 && !p.ck && p.batch <= 65535;
 }
 
 template <int IN, int OUT>
 hipError_t fwd_dispatch_n(ScanParams &p, int64_t N, void *stream, float *lent) {
-    if (tiled_ok(p, N, IN, OUT)) {
-        if (mbs::ts2::takes(p))
-            return p.z ? mbs::ts2::fwd_ts2<IN, OUT, true>(p, stream) : mbs::ts2::fwd_ts2<IN, OUT, false>(p, stream);
-        return p.z ? mbs::tiled::fwd_tiled<IN, OUT, true>(p, stream, lent)
-                   : mbs::tiled::fwd_tiled<IN, OUT, false>(p, stream, lent);
+    if (ring_ok(p, N)) {
+        if (short_ok(p))
+            return p.z ? mbs::tiled::fwd_short<IN, OUT, true>(p, stream) : mbs::tiled::fwd_short<IN, OUT, false>(p, stream);
+        return p.z ? mbs::ring::fwd_ring<IN, OUT, true>(p, stream, lent)
+                   : mbs::ring::fwd_ring<IN, OUT, false>(p, stream, lent);
     }
     switch (N) {
         case 1: return fwd_rowwise<IN, OUT, 1>(p, stream);
@@ -424,7 +428,7 @@ int scan_fwd_impl(const mb_scan_desc *desc, const void *u, const void *delta, co
         for (const Range &r : ins)
             if (overlaps(ck, ck_bytes, r.p, r.n)) return MB_ERR_ALIAS;
         if (overlaps(ck, ck_bytes, y, y_bytes) || overlaps(ck, ck_bytes, h_last, st_bytes)) return MB_ERR_ALIAS;
-        if (L > 0 && !tiled_ok(p, N, desc->in_dtype, desc->out_dtype)) return MB_ERR_UNSUPPORTED;
+        if (L > 0 && !ring_ok(p, N)) return MB_ERR_UNSUPPORTED;
         p.ck = ck;
     }
 
@@ -449,10 +453,10 @@ int scan_fwd_impl(const mb_scan_desc *desc, const void *u, const void *delta, co
     }
 
     float *lent = nullptr;
-    if (no_alloc && tiled_ok(p, N, desc->in_dtype, desc->out_dtype)) {
+    if (no_alloc && ring_ok(p, N)) {
         // the segment carry lives in this device's copy of the static scratch array
         int64_t seg_len, pieces;
-        const int64_t nseg = mbs::tiled::fwd_segments(p, &seg_len, &pieces);
+        const int64_t nseg = mbs::ring::segments(p, &seg_len, &pieces);
         const size_t need = mbs::tiled::fwd_carry_bytes(p, nseg, pieces);
         if (need > kScratchBytes) return MB_ERR_SHAPE;
         if (need > 0) {
