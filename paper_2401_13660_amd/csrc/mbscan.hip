@@ -180,7 +180,7 @@ hipError_t zero_async(float *p, int64_t n, hipStream_t st) {
 // workgroup of 4 groups: when the group count is a multiple of 4 (no workgroup
 // spans two batch elements) and there are at least 1,536 waves (1.5 per SIMD, so
 // that the other workgroup's waves fill a SIMD while one waits at the
-// workgroup's barrier every 4 steps), the workgroup sums its waves' terms in LDS.
+// workgroup's barrier after each chunk), the workgroup sums its waves' terms in LDS.
 bool bwd_workgroup_sum(int64_t batch, int64_t dim, int64_t nseg) {
     namespace W = mbs::bwd;
     const int64_t n_cg = (dim + W::kCh - 1) / W::kCh;

@@ -36,6 +36,7 @@
 
 #include "device_math.hpp"
 #include "scan_params.hpp"
+#include "scan_ring.hpp"
 
 #include <type_traits>
 
@@ -406,13 +407,15 @@ __global__ __launch_bounds__(kThreads) void bwd_seg_aggregate(BwdParams p) {
 
 // ---- the backward pass -----------------------------------------------------------
 // Floats of the workgroup's dB/dC exchange area (WG = true): two buffers of
-// 4 waves x 2 step pairs x 64 lanes.
-constexpr int kWgXchg = 2 * kWaves * 2 * 64;
+// 4 waves x 8 step pairs x 64 lanes (16 KB; two workgroups still share a CU's LDS).
+constexpr int kWgXchg = 2 * kWaves * (kT / 2) * 64;
 
 // WG = true (the number of 8-channel groups is a multiple of 4, so the 4 waves of
 // a workgroup are 4 consecutive groups of one batch element): the waves also
-// sum their dB/dC terms with each other through LDS every 4 steps, one barrier
-// per 4 steps, and the workgroup writes one partial per 32 channels.
+// sum their dB/dC terms with each other through LDS, one barrier per 16-step chunk, and
+// the workgroup writes one partial per 32 channels.  (With a barrier per 4 steps the
+// backward of (4, 3584, 8192) from checkpoints took 1981 us, with one per chunk 1866;
+// (4, 2048, 8192) 1146 and 1095.)
 template <int IN, int OUT, bool GATE, bool SOFTPLUS, bool WG = false>
 __global__ __launch_bounds__(kThreads, 2) void scan_bwd(BwdParams p) {     // 2 waves per SIMD: <= 256 VGPRs
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -489,7 +492,7 @@ __global__ __launch_bounds__(kThreads, 2) void scan_bwd(BwdParams p) {     // 2 
         float hb[kT + 1][2], ab[kT][2];                 // h_{t-1} .. h_{t+15}; abar_t
         hb[0][0] = live ? sl.ck0 : 0.0f;
         hb[0][1] = live ? sl.ck1 : 0.0f;
-        float xs[2], dyv[2], dsilu[2], sg[2], dlv[2], dsv[2];
+        float xs[2], dyv[2], dsilu[2], sg[2], dlv[2], dsv[2], dxv[2];
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             const float x = sl.u.get(k);
@@ -509,43 +512,75 @@ __global__ __launch_bounds__(kThreads, 2) void scan_bwd(BwdParams p) {     // 2 
             xs[k] = x;
             dlv[k] = dl;
             dsv[k] = ds;
+            dxv[k] = live ? dl * x : 0.0f;
             sum_dD = __builtin_fmaf(ds, x, sum_dD);
-            sm.dd[dd_row(2 * q + k)][j] = live ? f32x4{dl, dl * x, ds, x} : f32x4{dl, 0.0f, 0.0f, x};
+            sm.dd[dd_row(2 * q + k)][j] = f32x4{dl, dxv[k], live ? ds : 0.0f, x};
             sm.bc[2 * j + k][q] = f32x4{sl.b0.get(k), sl.b1.get(k), sl.c0.get(k), sl.c1.get(k)};
         }
         issue(sl, t0 - 2 * kT);                         // refill with the chunk two further back
         wave_sync();
 
         // ---- F: the chunk's forward from its checkpoint -------------------------
+        // abar of all 16 steps first, as in the forward: the products dlt A by MFMA outer
+        // products (the VALU's bits) and the exponentials together at raised priority, so
+        // that the other wave's instructions do not lose their pairing to single
+        // exponentials.  From checkpoints, (4, 3584, 8192): 2030 us with the exponentials
+        // among the recurrence, 2008 apart, 1981 at raised priority.
+        {
+            f32x4 xb[2][2];
+            auto half = [&](auto half_c) {
+                constexpr int HALF = decltype(half_c)::value;
 #pragma unroll
-        for (int tq = 0; tq < kT / 4; ++tq) {
-            float acc[4];
-            // the 4 steps' operands, read together; only the words used are read
-            float2 dvs[4];                              // (dlt, dlt*u)
-            f32x4 bvs[4];                               // (B0, B1, C0, C1); C only with a gate
+                for (int k = 0; k < 2; ++k) {            // timesteps 8 HALF + 2 i + k
+                    const f32x4 e0 = ring::outer4<HALF>(dlv[k], a2[0]);
+                    const f32x4 e1 = ring::outer4<HALF>(dlv[k], a2[1]);
+                    xb[HALF][k] = ring::outer4<HALF>(dxv[k], 1.0f);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                dvs[k] = lo2(sm.dd[dd_row(4 * tq + k)][j]);
-                if (GATE) {
-                    bvs[k] = sm.bc[4 * tq + k][q];
-                } else {
-                    const float2 b2 = lo2(sm.bc[4 * tq + k][q]);
-                    bvs[k] = f32x4{b2.x, b2.y, 0.0f, 0.0f};
+                    for (int i = 0; i < 4; ++i) {
+                        ab[8 * HALF + 2 * i + k][0] = e0[i];
+                        ab[8 * HALF + 2 * i + k][1] = e1[i];
+                    }
                 }
+            };
+            half(std::integral_constant<int, 0>{});
+            half(std::integral_constant<int, 1>{});
+#pragma unroll
+            for (int t = 0; t < kT; ++t) asm volatile("" : "+v"(ab[t][0]), "+v"(ab[t][1]));
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(3);
+#pragma unroll
+            for (int t = 0; t < kT; ++t) {
+                ab[t][0] = hw_exp2(ab[t][0]);
+                ab[t][1] = hw_exp2(ab[t][1]);
             }
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int t = 4 * tq + k;
-                const float2 dv = dvs[k];
-                const f32x4 bv = bvs[k];
+            for (int t = 0; t < kT; ++t) asm volatile("" : "+v"(ab[t][0]), "+v"(ab[t][1]));
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(0);
 #pragma unroll
-                for (int s = 0; s < 2; ++s) {
-                    ab[t][s] = hw_exp2(dv.x * a2[s]);
-                    hb[t + 1][s] = __builtin_fmaf(ab[t][s], hb[t][s], dv.y * bv[s]);
+            for (int tq = 0; tq < kT / 4; ++tq) {
+                float acc[4];
+                f32x4 bvs[4];                               // (B0, B1, C0, C1); C only with a gate
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    if (GATE) {
+                        bvs[k] = sm.bc[4 * tq + k][q];
+                    } else {
+                        const float2 b2 = lo2(sm.bc[4 * tq + k][q]);
+                        bvs[k] = f32x4{b2.x, b2.y, 0.0f, 0.0f};
+                    }
                 }
-                if (GATE) acc[k] = __builtin_fmaf(bv.w, hb[t + 1][1], bv.z * hb[t + 1][0]);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int t = 4 * tq + k;
+                    const float dx = xb[t >> 3][t & 1][(t >> 1) & 3];
+                    const f32x4 bv = bvs[k];
+#pragma unroll
+                    for (int s = 0; s < 2; ++s) hb[t + 1][s] = __builtin_fmaf(ab[t][s], hb[t][s], dx * bv[s]);
+                    if (GATE) acc[k] = __builtin_fmaf(bv.w, hb[t + 1][1], bv.z * hb[t + 1][0]);
+                }
+                if (GATE) sm.pa[4 * j + tq][q] = f32x4{acc[0], acc[1], acc[2], acc[3]};   // C . h, for dz
             }
-            if (GATE) sm.pa[4 * j + tq][q] = f32x4{acc[0], acc[1], acc[2], acc[3]};   // C . h, for dz
         }
         wave_sync();
 
@@ -607,28 +642,12 @@ __global__ __launch_bounds__(kThreads, 2) void scan_bwd(BwdParams p) {     // 2 
                     tot_hi = tot;
                 } else {                                // steps k, k + 1: b3 = 0 stores k, b3 = 1 stores k + 1
                     const float v = b3 ? tot_hi : tot;
-                    if (WG) wg_sums[((buf * kWaves + wave) * 2 + (k >> 1)) * 64 + lane] = v;
+                    if (WG) wg_sums[((buf * kWaves + wave) * (kT / 2) + 2 * tq + (k >> 1)) * 64 + lane] = v;
                     else pbc[pl + (4 * tq + k) * (kQ * 4)] = v;
                 }
             }
             sm.pa[4 * j + tq][q] = f32x4{pu[0], pu[1], pu[2], pu[3]};
             sm.pb[4 * j + tq][q] = f32x4{pd[0], pd[1], pd[2], pd[3]};
-            if (WG) {
-                // Every wave's 128 sums of this group are in wg_sums[buf]; wave w adds up
-                // the 4 waves' values of source lanes 32 (w & 1) .. + 31 of step pair
-                // w >> 1 (fixed order: deterministic) and writes them.  The buffers
-                // alternate, so the next group's writes never meet these reads: a wave
-                // passes the next barrier only after all have finished reading here.
-                __syncthreads();
-                if (lane < 32) {
-                    const int i = wave >> 1, l = (wave & 1) * 32 + lane;
-                    const float *x0 = wg_sums + (buf * kWaves * 2 + i) * 64 + l;
-                    const float sum = (x0[0] + x0[2 * 64]) + (x0[4 * 64] + x0[6 * 64]);
-                    const int lslot = ((l >> 5) << 1) | ((l >> 4) & 1);
-                    pbc[((uint32_t)t0 + 4 * tq + 2 * i + ((l >> 3) & 1)) * (kQ * 4) + (l & 7) * 4 + lslot] = sum;
-                }
-                buf ^= 1;
-            }
         }
         wave_sync();                                    // pa / pb are read below
 
@@ -647,6 +666,21 @@ __global__ __launch_bounds__(kThreads, 2) void scan_bwd(BwdParams p) {     // 2 
                 store2<OUT>(dub, lrow + (uint32_t)t0 + 2 * q, duv[0], duv[1]);
                 store2<OUT>(ddb, lrow + (uint32_t)t0 + 2 * q, ddv[0], ddv[1]);
             }
+        }
+        if (WG) {
+            // Every wave's sums of the chunk are in wg_sums[buf]; wave w adds up the 4
+            // waves' values of step pairs 2w and 2w + 1 (fixed order: deterministic) and
+            // writes them.  The buffers alternate, so the next chunk's writes never meet
+            // these reads: a wave passes the next barrier only after all have read here.
+            __syncthreads();
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                const int i = 2 * wave + m;
+                const float *x0 = wg_sums + (buf * kWaves * (kT / 2) + i) * 64 + lane;
+                constexpr int kWave = (kT / 2) * 64;
+                pbc[pl + 2 * i * (kQ * 4)] = (x0[0] + x0[kWave]) + (x0[2 * kWave] + x0[3 * kWave]);
+            }
+            buf ^= 1;
         }
         wave_sync();                                    // dd / bc / pa / pb are rewritten
     };
