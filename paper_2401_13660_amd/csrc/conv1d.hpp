@@ -166,52 +166,143 @@ __global__ __launch_bounds__(kThreads) void conv1d_fwd_vec(ConvParams p, uint32_
     }
 }
 
-// Every other shape: one span of 8 per thread, element loads with bounds checks.
-// A block covers 256 consecutive spans of one row.
+// Every other shape (L not a multiple of 8, or rows of x or y that start at any element):
+// the same spans and loads, 16-byte vectors aligned to their element only (the hardware
+// takes them), a row's short last span stored by elements.  With element loads
+// (one span per thread, 256 spans of one row per workgroup) bf16 (4, 3584, 8191) took 272
+// us and (1, 3584, 8188) 73; this way 112 and 25.  The multiple-of-8, 16-byte aligned
+// shapes keep conv1d_fwd_vec, which needs no division before its loads: 78 us for
+// (4, 3584, 8192).
+typedef u32x4 u32x4_e2 __attribute__((aligned(2)));
+typedef u32x2 u32x2_e2 __attribute__((aligned(2)));
+typedef f32x4 f32x4_e4 __attribute__((aligned(4)));
+
+// 8 activations and the H before them, as loaded: nothing is unpacked, and so nothing
+// waited for, before every load of the thread is on its way.
+template <int DT> struct RawSpan;
+template <> struct RawSpan<1> {
+    u32x4 v;
+    u32x2 t;                                             // the 4 before
+    __device__ __forceinline__ void load(const void *base, int64_t off) {
+        v = *reinterpret_cast<const u32x4_e2 *>(static_cast<const uint16_t *>(base) + off);
+    }
+    __device__ __forceinline__ void load_first(const void *base, int64_t off, int n) {
+        const uint16_t *at = static_cast<const uint16_t *>(base) + off;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            v[i] = (2 * i < n ? at[2 * i] : 0u) | (2 * i + 1 < n ? (uint32_t)at[2 * i + 1] << 16 : 0u);
+    }
+    __device__ __forceinline__ void load_before(const void *base, int64_t off) {
+        t = *reinterpret_cast<const u32x2_e2 *>(static_cast<const uint16_t *>(base) + off - 4);
+    }
+    __device__ __forceinline__ float get(int i) const { return i & 1 ? bf16_hi(v[i >> 1]) : bf16_lo(v[i >> 1]); }
+    __device__ __forceinline__ float before(int i) const { return i & 1 ? bf16_lo(t[1 - (i >> 1)]) : bf16_hi(t[1 - (i >> 1)]); }
+};
+template <> struct RawSpan<0> {
+    f32x4 v[2];
+    float t[3];
+    __device__ __forceinline__ void load(const void *base, int64_t off) {
+        const f32x4_e4 *p = reinterpret_cast<const f32x4_e4 *>(static_cast<const float *>(base) + off);
+        v[0] = p[0];
+        v[1] = p[1];
+    }
+    __device__ __forceinline__ void load_first(const void *base, int64_t off, int n) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i >> 2][i & 3] = i < n ? static_cast<const float *>(base)[off + i] : 0.0f;
+    }
+    __device__ __forceinline__ void load_before(const void *base, int64_t off) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) t[i] = static_cast<const float *>(base)[off - 1 - i];
+    }
+    __device__ __forceinline__ float get(int i) const { return v[i >> 2][i & 3]; }
+    __device__ __forceinline__ float before(int i) const { return t[i]; }
+};
+template <int DT> __device__ __forceinline__ void store8_any(void *base, int64_t off, const float (&v)[kSpan]) {
+    if constexpr (DT == 1) {
+        u32x4 r;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r[i] = bf16x2_pack(v[2 * i], v[2 * i + 1]);
+        *reinterpret_cast<u32x4_e2 *>(static_cast<uint16_t *>(base) + off) = r;
+    } else {
+        f32x4_e4 *p = reinterpret_cast<f32x4_e4 *>(static_cast<float *>(base) + off);
+        p[0] = f32x4{v[0], v[1], v[2], v[3]};
+        p[1] = f32x4{v[4], v[5], v[6], v[7]};
+    }
+}
+
 template <int IN, int OUT, int K>
-__global__ __launch_bounds__(kThreads) void conv1d_fwd(ConvParams p, uint32_t blocks_per_row) {
+__global__ __launch_bounds__(kThreads) void conv1d_fwd_any(ConvParams p, uint32_t nspan, uint32_t total) {
     constexpr int H = K - 1;
     const int64_t L = p.seqlen;
-    const uint32_t blk = blockIdx.x;
-    const int64_t row = blk / blocks_per_row;                        // wave-uniform
-    const int64_t c = (int64_t)(blk - (uint32_t)row * blocks_per_row) * kThreads + threadIdx.x;
-    const int64_t d = (uint32_t)row % (uint32_t)p.dim;
-    const int64_t t0 = c * kSpan;
-    const int64_t base = row * L;
-    if (t0 >= L) return;                         // the row's last block may run past its end
-
-    // xin[0 .. H-1] = inputs t0-H .. t0-1, xin[H .. H+7] = inputs t0 .. t0+7
-    float xin[H + kSpan];
+    const uint32_t first = (blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)) * (64 * kVecPerThread) +
+                           (threadIdx.x & 63);
+    const int64_t elems = p.batch * p.dim * L;
+    RawSpan<IN> raw[kVecPerThread];
+    float w[kVecPerThread][K], bv[kVecPerThread], st[kVecPerThread][H > 0 ? H : 1];
+    uint32_t row[kVecPerThread], sp[kVecPerThread];
 #pragma unroll
-    for (int i = 0; i < kSpan; ++i) xin[H + i] = t0 + i < L ? Act<IN>::ld(p.x, base + t0 + i) : 0.0f;
-#pragma unroll
-    for (int j = 0; j < H; ++j) {
-        const int64_t s = t0 - H + j;
-        xin[j] = s >= 0 ? Act<IN>::ld(p.x, base + s) : (p.state_in ? p.state_in[row * H + (H + s)] : 0.0f);
-    }
-
-    float w[K];
-#pragma unroll
-    for (int i = 0; i < K; ++i) w[i] = p.w[d * K + i];
-    const float b = p.bias ? p.bias[d] : 0.0f;
-    float out[kSpan];
-#pragma unroll
-    for (int i = 0; i < kSpan; ++i) {
-        float acc = b;
-#pragma unroll
-        for (int k = 0; k < K; ++k) acc = __builtin_fmaf(w[k], xin[i + k], acc);
-        out[i] = p.apply_silu ? silu_f32(acc) : acc;
+    for (int v = 0; v < kVecPerThread; ++v) {
+        // a span past the last one reads the last span again (never stored)
+        const uint32_t g = first + v * 64 < total ? first + v * 64 : total - 1;
+        row[v] = g / nspan;
+        sp[v] = g - row[v] * nspan;
+        const int64_t off = row[v] * L + (int64_t)sp[v] * kSpan;
+        // a row's short last span reads on into the next row (what it finds there is not
+        // used), but for the tensor's last
+        if (off + kSpan <= elems) raw[v].load(p.x, off);
+        else raw[v].load_first(p.x, off, (int)(elems - off));
+        // the inputs before a row's first span come from the state
+        if constexpr (H > 0) {
+            if (sp[v] > 0) raw[v].load_before(p.x, off);
+        }
     }
 #pragma unroll
-    for (int i = 0; i < kSpan; ++i)
-        if (t0 + i < L) st_out<OUT>(p.y, base + t0 + i, out[i]);
-
-    // The span holding the last input writes the next state: inputs L-H .. L-1.
-    if (H > 0 && p.state_out && t0 + kSpan >= L) {
+    for (int v = 0; v < kVecPerThread; ++v) {
+        const uint32_t d = row[v] % (uint32_t)p.dim;
 #pragma unroll
-        for (int j = 0; j < H; ++j) {
-            const int64_t s = L - H + j;                  // >= t0 - H: inside xin
-            p.state_out[row * H + j] = xin[s - t0 + H];
+        for (int i = 0; i < K; ++i) w[v][i] = p.w[d * K + i];
+        bv[v] = p.bias ? p.bias[d] : 0.0f;
+#pragma unroll
+        for (int j = 0; j < H; ++j)
+            st[v][j] = (sp[v] == 0 && p.state_in) ? p.state_in[(int64_t)row[v] * H + j] : 0.0f;
+    }
+#pragma unroll
+    for (int v = 0; v < kVecPerThread; ++v) {
+        if (first + v * 64 >= total) break;
+        const int64_t off = row[v] * L + (int64_t)sp[v] * kSpan;
+        const bool last = sp[v] == nspan - 1;
+        const int n = last ? (int)(L - (int64_t)sp[v] * kSpan) : kSpan;     // outputs of the span
+        float xin[H + kSpan];
+#pragma unroll
+        for (int i = 0; i < kSpan; ++i) xin[H + i] = raw[v].get(i);
+#pragma unroll
+        for (int j = 0; j < H; ++j) xin[j] = sp[v] > 0 ? raw[v].before(H - 1 - j) : st[v][j];
+        float out[kSpan];
+#pragma unroll
+        for (int i = 0; i < kSpan; ++i) {
+            float acc = bv[v];
+#pragma unroll
+            for (int k = 0; k < K; ++k) acc = __builtin_fmaf(w[v][k], xin[i + k], acc);
+            out[i] = p.apply_silu ? silu_f32(acc) : acc;
+        }
+        if (n == kSpan) {
+            store8_any<OUT>(p.y, off, out);
+        } else {
+#pragma unroll
+            for (int i = 0; i < kSpan; ++i)
+                if (i < n) st_out<OUT>(p.y, off + i, out[i]);
+        }
+        // the span holding the last input writes the next state: inputs L-H .. L-1, i.e.
+        // xin[n] .. xin[n + H - 1]
+        if (H > 0 && p.state_out && last) {
+#pragma unroll
+            for (int j = 0; j < H; ++j) {
+                float x = xin[kSpan + j];
+#pragma unroll
+                for (int m = 1; m < kSpan; ++m)
+                    if (n == m) x = xin[m + j];
+                p.state_out[(int64_t)row[v] * H + j] = x;
+            }
         }
     }
 }

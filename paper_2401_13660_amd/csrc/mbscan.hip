@@ -122,19 +122,13 @@ hipError_t conv_fwd_k(mbs::conv::ConvParams &p, bool vec, void *stream) {
     namespace C = mbs::conv;
     const int64_t nspan = (p.seqlen + C::kSpan - 1) / C::kSpan;
     const dim3 block(C::kThreads);
-    if (vec) {
-        uint32_t ns = (uint32_t)nspan, total = (uint32_t)(p.batch * p.dim * nspan);
-        const int64_t per_block = C::kThreads * C::kVecPerThread;
-        const dim3 grid((unsigned)((total + per_block - 1) / per_block));
-        void *args[] = {&p, &ns, &total};
-        return hipLaunchKernel(reinterpret_cast<const void *>(&C::conv1d_fwd_vec<IN, OUT, K>), grid, block,
-                               args, 0, static_cast<hipStream_t>(stream));
-    }
-    uint32_t per_row = (uint32_t)((nspan + C::kThreads - 1) / C::kThreads);
-    const dim3 grid((unsigned)(p.batch * p.dim * (int64_t)per_row));
-    void *args[] = {&p, &per_row};
-    return hipLaunchKernel(reinterpret_cast<const void *>(&C::conv1d_fwd<IN, OUT, K>), grid, block, args, 0,
-                           static_cast<hipStream_t>(stream));
+    uint32_t ns = (uint32_t)nspan, total = (uint32_t)(p.batch * p.dim * nspan);
+    const int64_t per_block = C::kThreads * C::kVecPerThread;
+    const dim3 grid((unsigned)((total + per_block - 1) / per_block));
+    void *args[] = {&p, &ns, &total};
+    const void *fn = vec ? reinterpret_cast<const void *>(&C::conv1d_fwd_vec<IN, OUT, K>)
+                         : reinterpret_cast<const void *>(&C::conv1d_fwd_any<IN, OUT, K>);
+    return hipLaunchKernel(fn, grid, block, args, 0, static_cast<hipStream_t>(stream));
 }
 
 template <int IN, int OUT, int K>

@@ -142,3 +142,24 @@ def test_conv_full_size_sampled_rows(name):
     rows = np.sort(np.random.default_rng(38).choice(nb * dim, 64, replace=False))
     announce(f"conv full size {name} {(nb, dim, L)}")
     run_conv(c, out_dtype=torch.bfloat16, rows=rows)
+
+
+@pytest.mark.parametrize("dtype,out", [("bf16", torch.bfloat16), ("bf16", torch.float32),
+                                       ("f32", torch.float32), ("f32", torch.bfloat16)])
+@pytest.mark.parametrize("width,L", [(4, 1), (4, 7), (3, 9), (2, 10), (4, 11), (4, 13), (1, 15), (4, 16), (3, 29)])
+def test_conv_short_last_spans_at_any_element(width, L, dtype, out):
+    """Every length of a row's last span, the tensor's last among them, with x and y that
+    start one element past an aligned address, and 17 rows in one workgroup."""
+    import paper_2401_13660_amd as mb
+    c = make_conv_inputs(1, 17, L, width, dtype=dtype, seed=90 + L, with_state=True)
+    announce(f"conv any element, width {width} L={L} {dtype} -> {out}")
+    y0, st0 = run_conv(c, out_dtype=out)
+    x = dev_tensor(c.x)
+    xs = torch.empty(x.numel() + 1, dtype=x.dtype, device=x.device)
+    xs[1:] = x.reshape(-1)
+    ys = torch.full((x.numel() + 2,), 7.0, dtype=out, device=x.device)      # one more on each side
+    y, st = mb.conv1d(xs[1:].view(x.shape), dev_tensor(c.w), bias=dev_tensor(c.bias), state=dev_tensor(c.state),
+                      out=ys[1:-1].view(x.shape), return_state=True)
+    torch.cuda.synchronize()
+    assert torch.equal(y, y0) and torch.equal(st, st0)
+    assert ys[0] == 7.0 and ys[-1] == 7.0
