@@ -16,6 +16,7 @@ import torch
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libmbscan.so")
+FAST_PATH = os.path.join(_PKG, "_fastcall.so")
 
 MB_F32, MB_BF16 = 0, 1
 _STATUS_OK = 0
@@ -38,12 +39,13 @@ class ConvDesc(ctypes.Structure):
 
 
 _lib = None
+_fast = None            # the native entry points for well-formed calls (csrc/fastcall.cpp)
 _VP = ctypes.c_void_p
 
 
 def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     """Load (once) and return the HIP library; raise loudly if it is not built."""
-    global _lib
+    global _lib, _fast
     if _lib is not None:
         return _lib
     if not os.path.exists(path):
@@ -71,8 +73,33 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.mb_status_string.restype = ctypes.c_char_p
     lib.mb_status_string.argtypes = [ctypes.c_int]
     lib.mb_abi_version.restype = ctypes.c_int
+    _fast = _load_fast(lib)
     _lib = lib
     return lib
+
+
+def _load_fast(lib):
+    """The module built from csrc/fastcall.cpp, calling the functions of ``lib``.  It takes
+    the calls whose tensors are plain, dense, of the expected shapes and on the current
+    device, does what the functions below do with them, and returns None for any other."""
+    if not os.path.exists(FAST_PATH):
+        raise MBScanError(f"{FAST_PATH} is not built; run `python -m paper_2401_13660_amd.build` "
+                          "(or __graft_entry__.build()) first")
+    if _raw_stream is None or _cur_device is None:
+        return None
+    from . import _fastcall
+    at = [ctypes.cast(fn, _VP).value for fn in (lib.mb_scan_fwd, lib.mb_scan_fwd_states, lib.mb_scan_fwd_ckpt,
+                                                lib.mb_scan_step, lib.mb_conv1d_fwd, lib.mb_conv1d_step,
+                                                lib.mb_verify_rank)]
+    _fastcall.setup(*at, _cur_device, _raw_stream, torch.nn.Parameter)
+    return _fastcall
+
+
+def _done(res, what):
+    """The result of a native entry point: what it returned, or the library's refusal."""
+    if type(res) is int:
+        _check(res, what)
+    return res
 
 
 def _check(status: int, what: str):
@@ -94,9 +121,9 @@ def _ptr(t):
 
 
 # Per-call host work bounds a decode step called from Python (the kernel of a
-# one-byte step takes a few microseconds), so the stream and device lookups use
-# torch's raw accessors where it has them, and a well-formed argument passes its
-# checks in one expression.
+# one-byte step takes a few microseconds): well-formed calls go through _fastcall.
+# What it does not take comes here, and the stream and device lookups use torch's raw
+# accessors where it has them.
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 _cur_device = getattr(torch._C, "_cuda_getDevice", None)
 
@@ -150,6 +177,12 @@ def scan_fwd(u, delta, A, B, C, D=None, dt_bias=None, z=None, h0=None, *, delta_
     (L // 16, batch, dim, N) (mb_scan_fwd_ckpt; not combined with positions).
     """
     lib = load_library()
+    if _fast is not None:
+        res = _fast.scan_fwd(u, delta, A, B, C, D, dt_bias, z, h0, delta_softplus, out_dtype, return_last_state, out,
+                             h_last, positions, h_at, return_ckpt, ck)
+        if res is not None:
+            return _done(res, "mb_scan_fwd_ckpt" if return_ckpt or ck is not None
+                         else "mb_scan_fwd" if positions is None else "mb_scan_fwd_states")
     if not isinstance(u, torch.Tensor) or u.dim() != 3:
         raise MBScanError("u must be a (batch, dim, L) tensor")
     nb, dim, L = u.shape
@@ -261,6 +294,10 @@ def scan_step(h, u_t, delta_t, A, B_t, C_t, D=None, dt_bias=None, z_t=None, *, d
               out_dtype=torch.float32, out=None):
     """One recurrent step; h (batch, dim, N) fp32 is updated in place.  Returns y_t (batch, dim)."""
     lib = load_library()
+    if _fast is not None:
+        res = _fast.scan_step(h, u_t, delta_t, A, B_t, C_t, D, dt_bias, z_t, delta_softplus, out_dtype, out)
+        if res is not None:
+            return _done(res, "mb_scan_step")
     if not isinstance(h, torch.Tensor) or h.dim() != 3:
         raise MBScanError("h must be a (batch, dim, N) tensor")
     nb, dim, N = h.shape
@@ -298,6 +335,10 @@ def conv1d(x, w, bias=None, state=None, *, apply_silu=True, out_dtype=None, retu
     None).  Returns y, or (y, state_out) where state_out holds the last k-1 inputs.
     """
     lib = load_library()
+    if _fast is not None:
+        res = _fast.conv1d(x, w, bias, state, apply_silu, out_dtype, return_state, out, state_out)
+        if res is not None:
+            return _done(res, "mb_conv1d_fwd")
     if not isinstance(x, torch.Tensor) or x.dim() != 3:
         raise MBScanError("x must be a (batch, dim, L) tensor")
     nb, dim, L = x.shape
@@ -332,6 +373,10 @@ def conv1d_step(state, x_t, w, bias=None, *, apply_silu=True, out_dtype=None, ou
     """One byte of the convolution; state (batch, dim, k-1) fp32 is updated in place.
     Returns y_t (batch, dim)."""
     lib = load_library()
+    if _fast is not None:
+        res = _fast.conv1d_step(state, x_t, w, bias, apply_silu, out_dtype, out)
+        if res is not None:
+            return _done(res, "mb_conv1d_step")
     if not isinstance(x_t, torch.Tensor) or x_t.dim() != 2:
         raise MBScanError("x_t must be a (batch, dim) tensor")
     nb, dim = x_t.shape
@@ -363,6 +408,10 @@ def verify_rank(logits, draft, beta, *, return_ranks=False):
     draft: int32 (batch, ndraft).  Returns (accepted, last_pos), each int32 (batch,),
     and the int32 (batch, ndraft) ranks when ``return_ranks``."""
     lib = load_library()
+    if _fast is not None:
+        res = _fast.verify_rank(logits, draft, beta, return_ranks)
+        if res is not None:
+            return _done(res, "mb_verify_rank")
     if not isinstance(logits, torch.Tensor) or logits.dim() != 3:
         raise MBScanError("logits must be a (batch, ndraft, vocab) tensor")
     nb, n, V = logits.shape

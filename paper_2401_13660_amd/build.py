@@ -1,4 +1,5 @@
-"""Build the HIP library libmbscan.so in-tree (gfx950 only), the issue-rate
+"""Build the HIP library libmbscan.so in-tree (gfx950 only), the binding's native entry
+points (csrc/fastcall.cpp), the issue-rate
 micro-benchmark behind the instruction cost model (csrc/issue_rates.hip), the
 LDS bank probe behind the time-split kernel's tables (csrc/lds_banks.hip), and
 the exhaustive check of the bf16 pair conversion (csrc/bf16_pack_check.hip).
@@ -40,10 +41,35 @@ def build(verbose: bool = False) -> str:
         sys.stderr.write(res.stdout + res.stderr)
         raise RuntimeError("hipcc failed to build libmbscan.so")
     os.replace(tmp, LIB)
+    build_fastcall(verbose)
     build_issue_rates(verbose)
     build_lds_banks(verbose)
     build_bf16_pack_check(verbose)
     return LIB
+
+
+def build_fastcall(verbose: bool = False) -> str:
+    """The binding's native entry points (csrc/fastcall.cpp), against the installed torch."""
+    import sysconfig
+
+    import torch
+    base = os.path.dirname(torch.__file__)
+    out = os.path.join(PKG, "_fastcall.so")
+    tmp = out + ".tmp"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unused-function",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", os.path.join(ROOT, "include"),
+           "-isystem", os.path.join(base, "include"),
+           "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "fastcall.cpp"), "-o", tmp,
+           "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd))
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        sys.stderr.write(res.stdout + res.stderr)
+        raise RuntimeError("the C++ compiler failed to build _fastcall.so")
+    os.replace(tmp, out)
+    return out
 
 
 def build_tool(name: str, verbose: bool = False) -> str:

@@ -1,0 +1,131 @@
+"""The binding's native entry points against its Python code.
+
+Well-formed calls go through _fastcall; the same call with it switched off runs the checks
+and allocations of the Python functions.  Both make one library call on the same inputs, so
+every result must be the same bits, with the same number of outputs, types and shapes; and
+what the native entry points do not take must end in the same errors.
+"""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import announce, dev_tensor, has_gpu, to_device
+from paper_2401_13660_amd.inputs import make_conv_inputs, make_inputs
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not has_gpu(), reason="needs a GPU")]
+
+
+@pytest.fixture
+def both(monkeypatch):
+    """both(call): its results through the native entry points and through Python."""
+    from paper_2401_13660_amd import _binding
+    _binding.load_library()
+    assert _binding._fast is not None
+
+    def run(call):
+        out = []
+        for native in (True, False):
+            with monkeypatch.context() as m:
+                if not native:
+                    m.setattr(_binding, "_fast", None)
+                r = call()
+                torch.cuda.synchronize()
+            out.append(r if isinstance(r, tuple) else (r,))
+        return out
+    return run
+
+
+def _same(a, b):
+    assert len(a) == len(b)
+    for x, y in zip(a, b):
+        assert x.dtype == y.dtype and x.shape == y.shape and x.device == y.device
+        assert torch.equal(torch.nan_to_num(x.float(), nan=7.0), torch.nan_to_num(y.float(), nan=7.0))
+
+
+@pytest.mark.parametrize("dtype,out_dtype", [("bf16", torch.float32), ("bf16", torch.bfloat16), ("f32", torch.float32)])
+@pytest.mark.parametrize("opts", ["plain", "last", "given", "positions", "ckpt", "bare"])
+def test_scan_fwd(both, dtype, out_dtype, opts):
+    import paper_2401_13660_amd as mb
+    inp = make_inputs(2, 24, 48, 16, dtype=dtype, seed=3, with_h0=True)
+    t = to_device(inp)
+    kw = dict(D=t["Dskip"], dt_bias=t["dt_bias"], z=t["z"], h0=t["h0"], out_dtype=out_dtype)
+    if opts == "bare":
+        kw = dict(delta_softplus=False)
+    if opts == "last":
+        kw["return_last_state"] = True
+    if opts == "positions":
+        kw["positions"] = torch.tensor([[0, 47], [-1, 99]], dtype=torch.int32, device="cuda:0")
+    if opts == "ckpt":
+        kw.update(return_ckpt=True, return_last_state=True)
+
+    def call():
+        k = dict(kw)
+        if opts == "given":
+            k.update(out=torch.zeros((2, 24, 48), dtype=out_dtype, device="cuda:0"), h_last=torch.zeros_like(t["h0"]))
+        return mb.scan_fwd(t["u"], t["delta"], torch.nn.Parameter(t["A"]), t["B"], t["C"], **k)
+
+    announce(f"fastcall scan_fwd {dtype} {opts}")
+    _same(*both(call))
+
+
+@pytest.mark.parametrize("given", [False, True])
+def test_steps_convolution_and_rank(both, given):
+    import paper_2401_13660_amd as mb
+    inp = make_inputs(3, 40, 1, 16, seed=4, with_h0=True)
+    c = make_conv_inputs(3, 40, 21, 4, dtype="bf16", seed=5, with_state=True)
+    t = to_device(inp)
+    x, w, bias, st = (dev_tensor(v) for v in (c.x, c.w, c.bias, c.state))
+    out = torch.empty((3, 40), dtype=torch.bfloat16, device="cuda:0") if given else None
+    flat = {k: t[k][..., 0].contiguous() for k in ("u", "delta", "B", "C", "z")}
+    announce(f"fastcall steps, out given: {given}")
+
+    def step():
+        h = t["h0"].clone()
+        return mb.scan_step(h, flat["u"], flat["delta"], t["A"], flat["B"], flat["C"], D=t["Dskip"],
+                            dt_bias=t["dt_bias"], z_t=flat["z"], out=None if out is None else out.clone()), h
+
+    def conv_step():
+        s = st.clone()
+        return mb.conv1d_step(s, x[..., 0].contiguous(), w, bias, out=None if out is None else out.clone()), s
+
+    logits = torch.randn(3, 5, 256, device="cuda:0")
+    draft = logits.argsort(-1)[..., -2].to(torch.int32).contiguous()
+    for call in (step, conv_step, lambda: mb.conv1d(x, w, bias, state=st, return_state=True),
+                 lambda: mb.conv1d(x, w, apply_silu=False, out_dtype=torch.float32),
+                 lambda: mb.verify_rank(logits, draft, 3, return_ranks=True), lambda: mb.verify_rank(logits, draft, 1)):
+        _same(*both(call))
+
+
+def test_refusals_and_errors_are_the_same(both):
+    import paper_2401_13660_amd as mb
+    inp = make_inputs(2, 24, 48, 16, seed=6, with_h0=True)
+    t = to_device(inp)
+    a = dict(u=t["u"], delta=t["delta"], A=t["A"], B=t["B"], C=t["C"])
+
+    class Tagged(torch.Tensor):
+        pass
+
+    cases = [dict(a, u=t["u"].cpu()), dict(a, delta=t["delta"].transpose(1, 2)), dict(a, B=t["B"][:, :8]),
+             dict(a, A=t["A"].double()), dict(a, h0=t["h0"][:1]), dict(a, out=t["u"]), dict(a, u=None),
+             dict(a, out_dtype=torch.float16), dict(a, C=t["C"].float()),
+             dict(a, positions=torch.zeros((1, 2), dtype=torch.int64, device="cuda:0"))]
+    for kw in cases:
+        said = []
+
+        def call():
+            try:
+                mb.scan_fwd(**kw)
+                said.append(None)
+            except mb.MBScanError as e:
+                said.append(str(e))
+            return torch.zeros(1)
+
+        both(call)
+        assert said[0] is not None and said[0] == said[1], said
+    # a subclass is no plain tensor: the Python code takes it
+    _same(*both(lambda: mb.scan_fwd(**dict(a, u=t["u"].as_subclass(Tagged)))))
+    # outputs of a call under no stream but torch's current one
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        _same(*both(lambda: mb.scan_fwd(**a)))
