@@ -426,8 +426,9 @@ int scan_fwd_impl(const mb_scan_desc *desc, const void *u, const void *delta, co
         p.ck = ck;
     }
 
-    if (npos > 0) {
-        // Position -1 and invalid positions, before h_last (which may be h0) is written.
+    if (npos > 0 && (L == 0 || !ring_ok(p, N))) {
+        // Position -1 and invalid positions, before h_last (which may be h0) is written; at
+        // dstate 16 the scan's kernels fill these slots themselves.
         const dim3 block(256), grid((unsigned)((hpos_elems + 255) / 256));
         int64_t n_arg = N;
         void *args[] = {&p, &n_arg};

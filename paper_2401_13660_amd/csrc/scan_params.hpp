@@ -13,12 +13,13 @@ struct ScanParams {
     float *h_last;
     // States at requested positions: pos[k * batch + b] is position k of batch
     // element b; h_pos[((k * batch + b) * dim + d) * N + n] receives the state
-    // after that timestep.  npos == 0 disables them.  The scan kernels write
-    // only positions in [0, seqlen); init_positions fills the other slots.
+    // after that timestep.  npos == 0 disables them.  The row kernel
+    // writes only positions in [0, seqlen), and init_positions the other slots; the
+    // kernels of dstate 16 write all.
     const int32_t *pos;
     int64_t npos;
     float *h_pos;
-    // Checkpoints for the backward (tiled path only): ck[((t / 16) * batch * dim
+    // Checkpoints for the backward (ring kernel only): ck[((t / 16) * batch * dim
     // + row) * 16 + n] receives the state before timestep t for every t that is a
     // multiple of 16 (h0 at t = 0).  Null disables them.
     float *ck;

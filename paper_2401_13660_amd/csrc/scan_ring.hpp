@@ -226,6 +226,20 @@ __global__ __launch_bounds__(kMaxWaves * 64) void scan_fwd_ring(ScanParams p, Ri
     const float dskip = p.Dskip ? p.Dskip[dcl] : 0.0f;
     const float bias = p.dt_bias ? p.dt_bias[dcl] : 0.0f;
 
+    // Positions that no slice holds: -1 is the state before the first timestep, one past
+    // either end reads NaN.  (As a kernel of its own before the scan this took 2-3 us.)
+    if constexpr (REC == kPositions) {
+        if (r == 0 && seg == 0) {
+            for (int64_t k = 0; k < p.npos; ++k) {
+                const int64_t pk = p.pos[k * p.batch + b];              // wave-uniform
+                if (pk >= 0 && pk < p.seqlen) continue;
+                float *dst = p.h_pos + ((k * p.batch + b) * p.dim + dcl) * kN + n0;
+                dst[0] = pk == -1 ? h[0] : __builtin_nanf("");
+                dst[1] = pk == -1 ? h[1] : __builtin_nanf("");
+            }
+        }
+    }
+
     // The state that slice s starts from, handed over by the wave of slice s - 1.  The
     // flag is read before the state it vouches for, and a wave's LDS operations are
     // carried out in order.

@@ -1,9 +1,8 @@
 // scan_rowwise.hpp -- the plain forward scan: one thread per (batch, channel) row.
 //
 // Each thread walks its row in time order, holding the N-state of eq. (2) in
-// registers.  It is the fallback for shapes the tiled kernel does not take
-// (dstate < 16, unaligned rows) and the baseline the tiled kernel is measured
-// against; it is correct for every legal argument combination.
+// registers.  It takes what the kernels of dstate 16 do not (dstate < 16, sequences of
+// 2^25 timesteps and more); it is correct for every legal argument combination.
 #pragma once
 
 #include "device_math.hpp"
@@ -59,7 +58,7 @@ __global__ __launch_bounds__(64) void scan_fwd_rowwise(ScanParams p) {
     }
 }
 
-// The slots of h_pos the scan kernels do not write: position -1 is the state
+// The slots of h_pos the row kernel does not write: position -1 is the state
 // before the first timestep (h0, or zeros), and a position outside
 // [-1, seqlen - 1] reads NaN.  One thread per (k, b, d, n).
 __global__ void init_positions(ScanParams p, int64_t N) {

@@ -300,10 +300,11 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_short(ScanParams p) {
     // phase B's operations in the same order, so that the recorded state equals the one
     // the scan carries.
     if constexpr (POS) for (int64_t k = 0; k < p.npos; ++k) {
+        // position -1 is the state before the first timestep, one past either end reads NaN
         const int64_t pk = p.pos[k * p.batch + b];              // wave-uniform
-        if (pk < 0 || pk >= kShort) continue;
-        float g0 = hs0, g1 = hs1;
-        for (int i = 0; i <= (int)pk; ++i) {
+        const bool none = pk < -1 || pk >= kShort;
+        float g0 = none ? __builtin_nanf("") : hs0, g1 = none ? __builtin_nanf("") : hs1;
+        for (int i = 0; !none && i <= (int)pk; ++i) {
             const f32x4 dv = sm.dd[i >> 1][j];
             const float dl = (i & 1) ? dv.z : dv.x;
             const float dx = (i & 1) ? dv.w : dv.y;
