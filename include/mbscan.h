@@ -120,11 +120,11 @@ int mb_scan_fwd(const mb_scan_desc *desc,
  * 8 MiB instead: each GPU the library runs on holds its own copy until the
  * process ends.  A problem whose carry would exceed it returns MB_ERR_SHAPE
  * (on a 256-CU MI355X the forward cuts fewer than 192 groups of 8 channels, and
- * into at most 1024 parts in all: below 2.3 MiB).  The array keeps the last call's contents; nothing in it needs to
- * start at zero (the segment pre-pass writes every carry entry before the scan
- * reads it).  Every call on one GPU shares that GPU's array, so calls that may
- * overlap in time on one GPU (other streams, other threads) race: serialise
- * them, or use mb_scan_fwd.
+ * into at most 1024 parts in all: below 2.3 MiB).  The array keeps the last
+ * call's contents; nothing in it needs to start at zero (the segment pre-pass
+ * writes every carry entry before the scan reads it).  Every call on one GPU
+ * shares that GPU's array, so calls that may overlap in time on one GPU (other
+ * streams, other threads) race: serialise them, or use mb_scan_fwd.
  */
 int mb_scan_fwd_noalloc(const mb_scan_desc *desc,
                         const void *u, const void *delta, const float *A,

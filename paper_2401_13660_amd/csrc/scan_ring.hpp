@@ -14,7 +14,7 @@
 //
 // What bounds it: instruction issue (an exponential holds its SIMD for 8 cycles, the VALU
 // instructions beside it take 4; 172 of these and 40 of those per slice make 1,050 cycles,
-// the 972M layer takes about 1,200).  With one wave per 8 channels for a whole sequence the
+// the 972M layer takes about 1,310).  With one wave per 8 channels for a whole sequence the
 // number of waves is batch * dim / 8, so that most shapes left SIMDs with one wave or two,
 // unevenly, or paid a pre-pass that repeated every exponential to cut the sequence.  Here
 // the waves per SIMD are a free choice (4, as many as 128 VGPRs allow), and with W a
