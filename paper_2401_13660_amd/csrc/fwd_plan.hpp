@@ -1,0 +1,145 @@
+// fwd_plan.hpp -- which kernel a forward scan takes and how its work is cut: rules on
+// sizes and alignment, in host code without a GPU call.
+#pragma once
+
+#include <stddef.h>
+#include <stdint.h>
+
+namespace mbs {
+namespace plan {
+
+constexpr int64_t kCh = 8;            // channels per chain
+constexpr int64_t kSlice = 16;        // timesteps per slice of the ring kernel
+
+enum Kernel {
+    kRow,                             // one thread per row (scan_rowwise.hpp)
+    kShort,                           // a sequence of 16 timesteps (scan_tiled.hpp)
+    kRing,                            // slices dealt round the waves of a workgroup (scan_ring.hpp)
+};
+
+struct Shape {
+    int64_t batch, dim, L, dstate;
+    bool aligned16;                   // every activation and y on a 16-byte boundary
+    bool ckpt;                        // checkpoints are stored
+};
+
+struct Fwd {
+    Kernel kernel;
+    int64_t chains;                   // of all time segments (kRing)
+    int64_t nseg, seg_len, pieces;    // time segments (1: none), their length, pre-pass pieces per segment
+    uint32_t log_w;                   // waves per chain: 1 << log_w
+    int64_t workgroups;
+    uint32_t threads;                 // per workgroup
+};
+
+// HIP refuses a launch whose workgroups times threads along a grid dimension do not fit
+// 32 bits.
+inline bool launch_fits(int64_t workgroups, uint32_t threads) {
+    return workgroups <= int64_t(0xFFFFFFFF) / threads;
+}
+
+// Chains of W waves in workgroups of 4 waves, or of W if that is more.
+inline uint32_t ring_threads(uint32_t log_w) { return 64u * (log_w > 2 ? 1u << log_w : 4u); }
+inline int64_t ring_workgroups(int64_t chains, uint32_t log_w) {
+    const int64_t per_wg = log_w > 2 ? 1 : 4 >> log_w;
+    return (chains + per_wg - 1) / per_wg;
+}
+
+// Waves per chain.  4 (one per SIMD) for most: measured with 1, 2, 4 and 8, bf16 in and
+// fp32 out, (4, 3584, 8192) took 546, 541, 492 and 559 us, (4, 2048, 8192) 410, 306, 292 and
+// 316, (1, 4608, 65536) 3123, 2296, 1583 and 1999, (1, 3584, 1013) 56, 34, 24 and 25: fewer
+// waves leave SIMDs unevenly filled or idle, more make the chain's hand-overs its pace.
+// 8 with at most one chain per CU ((1, 2048, 8192): 115 us with 4, 109 with 8).
+// With more than 4 chains per CU the waves of short sequences come in several rounds, where
+// each wave's start-up counts: 2 up to 16 slices ((4, 3584, 192): 16.7, 16.5, 18.1 and 25.8
+// us with 1, 2, 4 and 8; (4, 4608, 256): 28.0, 25.4, 25.4 and 36.0), 1 up to 4 slices
+// ((16, 3584, 48): 17.1, 19.6, 25.1 and 41.0).
+// Fewer where the launch would not fit a grid dimension otherwise.
+inline uint32_t waves_per_chain_log2(int64_t chains, int64_t slices, int64_t cus) {
+    uint32_t lw = chains <= cus ? 3 : 2;
+    if (chains > 4 * cus && slices <= 16) lw = slices <= 4 ? 0 : 1;
+    while (lw > 0 && ((int64_t(1) << lw) > slices || !launch_fits(ring_workgroups(chains, lw), ring_threads(lw)))) --lw;
+    return lw;
+}
+
+// Time segments of the forward.  With fewer than 3/8 `resident` waves (8 channels of one
+// batch element each, for the whole sequence) the sequence is cut into segments (each a
+// multiple of 32 bytes, at least 256).  A pre-pass computes each segment's aggregate from
+// a zero state; the scan of segment s then starts from h0 folded with the aggregates of
+// segments 0 .. s-1.  The count is the largest that gives at most 2 `resident` waves.
+// The caller's `resident` says what it fills the chip with; the ring kernel's is 2 per
+// CU (see segments).
+// The pre-pass cuts each segment into `pieces` (1 or 2) equal pieces, one wave
+// per piece and 8 channels.  A SIMD takes as long as its largest number of
+// waves times the piece length, so 2 pieces are taken where that is shorter:
+// ceil(2 w / simds) / 2 below ceil(w / simds), for the w waves of whole
+// segments.  That takes 2 pieces only up to 7 waves per SIMD, as many as fit
+// with bf16 inputs (70 VGPRs), so those waves are all resident at once.
+inline int64_t choose_segments(int64_t waves_base, int64_t L, int64_t resident, int64_t simds, int64_t *seg_len,
+                               int64_t *pieces) {
+    int64_t nseg = 1;
+    if (waves_base > 0 && waves_base * 8 < resident * 3) nseg = 2 * resident / waves_base;
+    const int64_t max_seg = L / 256;
+    if (nseg > max_seg) nseg = max_seg;
+    if (nseg < 1) nseg = 1;
+    int64_t m = 1;
+    if (nseg > 1) {
+        const int64_t w = waves_base * (nseg - 1);
+        if ((2 * w + simds - 1) / simds < 2 * ((w + simds - 1) / simds)) m = 2;
+    }
+    int64_t len = (L + nseg - 1) / nseg;
+    len = (len + 32 * m - 1) / (32 * m) * (32 * m);     // pieces of a multiple of 32 timesteps
+    *seg_len = len;
+    *pieces = m;
+    return (L + len - 1) / len;
+}
+
+// The time segments the forward takes (1: none), their length and the pre-pass
+// pieces per segment.  The pre-pass repeats the exponentials of all segments but the last,
+// so segments are taken only with fewer than 3/4 of a chain per CU, and then about 4 CUs'
+// worth of chains (4 workgroups each): (1, 1024, 8192), 128 chains, took 107 us unsegmented,
+// 76 in 4, 67 in 8 and 75 in 16 segments; (1, 2048, 8192), 256 chains, 107 unsegmented
+// against 116 or more; (1, 1536, 2048), 192 chains, 31 against 35.  A short sequence is
+// done before the pre-pass pays: (1, 1024, 1024) took 14 us unsegmented, 31 in 4 segments.
+inline int64_t segments(int64_t chains, int64_t L, int64_t cus, int64_t *seg_len, int64_t *pieces) {
+    *seg_len = L;
+    *pieces = 1;
+    return L >= 3072 ? choose_segments(chains, L, 2 * cus, 4 * cus, seg_len, pieces) : 1;
+}
+
+// The plan of a scan with at least one row and one timestep; cus_of says how many compute
+// units the device has, asked only where a rule needs it.
+inline Fwd fwd(const Shape &s, int64_t (*cus_of)()) {
+    Fwd f{kRow, 0, 1, s.L, 1, 0, 0, 64};
+    const int64_t rows = s.batch * s.dim, base = s.batch * ((s.dim + kCh - 1) / kCh);
+    f.workgroups = (rows + 63) / 64;
+    // The kernels of dstate 16 take any length below 2^25 (32-bit lane offsets inside a
+    // wave's rows: 16 rows x L x 4 bytes < 2^32) and as many chains as one wave each fits a
+    // launch (below 2^26); the row kernel's launch holds 8 times as many.
+    if (s.dstate != 16 || s.L >= (int64_t(1) << 25) || !launch_fits(ring_workgroups(base, 0), ring_threads(0))) return f;
+    // The 16-timestep kernel takes the verify shape: one slice, 16-byte aligned rows (its
+    // loads are wider), no checkpoints, the batch in the grid's second dimension.
+    if (s.L == 16 && s.aligned16 && !s.ckpt && s.batch <= 65535) {
+        f.kernel = kShort;
+        f.workgroups = ((s.dim + kCh - 1) / kCh + 3) / 4;
+        f.threads = 256;
+        return f;
+    }
+    const int64_t cus = cus_of();
+    f.kernel = kRing;
+    f.nseg = segments(base, s.L, cus, &f.seg_len, &f.pieces);
+    f.chains = base * f.nseg;
+    f.log_w = waves_per_chain_log2(f.chains, (f.seg_len + kSlice - 1) / kSlice, cus);
+    f.workgroups = ring_workgroups(f.chains, f.log_w);
+    f.threads = ring_threads(f.log_w);
+    return f;
+}
+
+// Device bytes of the segment carry: the aggregates of the pieces of segments
+// 0 .. nseg-2, then the copy of h0 (rows x 16 states x 2 floats per plane).
+inline size_t carry_bytes(int64_t rows, const Fwd &f) {
+    return f.nseg > 1 ? (size_t)(f.pieces * (f.nseg - 1) + 1) * (size_t)rows * 16 * 2 * sizeof(float) : 0;
+}
+
+}  // namespace plan
+}  // namespace mbs

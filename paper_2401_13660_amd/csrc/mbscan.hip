@@ -9,6 +9,7 @@
 #include <mutex>
 
 #include "conv1d.hpp"
+#include "fwd_plan.hpp"
 #include "mbscan.h"
 #include "scan_bwd.hpp"
 #include "scan_params.hpp"
@@ -63,30 +64,15 @@ hipError_t fwd_rowwise(ScanParams &p, void *stream) {
                   stream);
 }
 
-// The ring kernel takes dstate 16: any length below 2^25 (32-bit lane offsets inside a
-// wave's rows: 16 rows x L x 4 bytes < 2^32) and any row alignment, with fewer than 2^30
-// eight-channel chains (it indexes them in 32 bits; with time segments, only shapes of a
-// few hundred chains are multiplied).
-bool ring_ok(const ScanParams &p, int64_t N) {
-    return N == 16 && p.seqlen < (int64_t(1) << 25) && p.batch * ((p.dim + 7) / 8) < (int64_t(1) << 30);
-}
-
-// The 16-timestep kernel takes the verify shape: one slice, 16-byte aligned rows (its
-// loads are wider), no checkpoints, the batch in the grid's second dimension.
-bool short_ok(const ScanParams &p) {
-    const void *ptrs[] = {p.u, p.delta, p.z, p.Bm, p.Cm, p.y};
-    for (const void *q : ptrs)
-        if (q && !aligned(q, 16)) return false;
-    return p.seqlen == 16 && !p.ck && p.batch <= 65535;
-}
-
 template <int IN, int OUT>
-hipError_t fwd_dispatch_n(ScanParams &p, int64_t N, void *stream, float *lent) {
-    if (ring_ok(p, N)) {
-        if (short_ok(p))
+hipError_t fwd_dispatch_n(ScanParams &p, const mbs::plan::Fwd &f, int64_t N, void *stream, float *lent) {
+    switch (f.kernel) {
+        case mbs::plan::kShort:
             return p.z ? mbs::tiled::fwd_short<IN, OUT, true>(p, stream) : mbs::tiled::fwd_short<IN, OUT, false>(p, stream);
-        return p.z ? mbs::ring::fwd_ring<IN, OUT, true>(p, stream, lent)
-                   : mbs::ring::fwd_ring<IN, OUT, false>(p, stream, lent);
+        case mbs::plan::kRing:
+            return p.z ? mbs::ring::fwd_ring<IN, OUT, true>(p, f, stream, lent)
+                       : mbs::ring::fwd_ring<IN, OUT, false>(p, f, stream, lent);
+        default: break;
     }
     switch (N) {
         case 1: return fwd_rowwise<IN, OUT, 1>(p, stream);
@@ -422,11 +408,19 @@ int scan_fwd_impl(const mb_scan_desc *desc, const void *u, const void *delta, co
         for (const Range &r : ins)
             if (overlaps(ck, ck_bytes, r.p, r.n)) return MB_ERR_ALIAS;
         if (overlaps(ck, ck_bytes, y, y_bytes) || overlaps(ck, ck_bytes, h_last, st_bytes)) return MB_ERR_ALIAS;
-        if (L > 0 && !ring_ok(p, N)) return MB_ERR_UNSUPPORTED;
         p.ck = ck;
     }
 
-    if (npos > 0 && (L == 0 || !ring_ok(p, N))) {
+    mbs::plan::Fwd f{};
+    if (L > 0) {
+        bool aligned16 = true;
+        for (const void *q : {u, delta, z, Bmat, Cmat, static_cast<const void *>(y)})
+            if (q && !aligned(q, 16)) aligned16 = false;
+        f = mbs::plan::fwd({B, D, L, N, aligned16, ck != nullptr}, &mbs::tiled::device_cus);
+        if (ck && f.kernel != mbs::plan::kRing) return MB_ERR_UNSUPPORTED;
+    }
+
+    if (npos > 0 && (L == 0 || f.kernel == mbs::plan::kRow)) {
         // Position -1 and invalid positions, before h_last (which may be h0) is written; at
         // dstate 16 the scan's kernels fill these slots themselves.
         const dim3 block(256), grid((unsigned)((hpos_elems + 255) / 256));
@@ -448,11 +442,9 @@ int scan_fwd_impl(const mb_scan_desc *desc, const void *u, const void *delta, co
     }
 
     float *lent = nullptr;
-    if (no_alloc && ring_ok(p, N)) {
+    if (no_alloc) {
         // the segment carry lives in this device's copy of the static scratch array
-        int64_t seg_len, pieces;
-        const int64_t nseg = mbs::ring::segments(p, &seg_len, &pieces);
-        const size_t need = mbs::tiled::fwd_carry_bytes(p, nseg, pieces);
+        const size_t need = mbs::plan::carry_bytes(rows, f);
         if (need > kScratchBytes) return MB_ERR_SHAPE;
         if (need > 0) {
             const int st = scratch_for_current_device(reinterpret_cast<void **>(&lent));
@@ -462,11 +454,11 @@ int scan_fwd_impl(const mb_scan_desc *desc, const void *u, const void *delta, co
 
     hipError_t e;
     if (desc->in_dtype == MB_F32)
-        e = desc->out_dtype == MB_F32 ? fwd_dispatch_n<0, 0>(p, N, stream, lent)
-                                      : fwd_dispatch_n<0, 1>(p, N, stream, lent);
+        e = desc->out_dtype == MB_F32 ? fwd_dispatch_n<0, 0>(p, f, N, stream, lent)
+                                      : fwd_dispatch_n<0, 1>(p, f, N, stream, lent);
     else
-        e = desc->out_dtype == MB_F32 ? fwd_dispatch_n<1, 0>(p, N, stream, lent)
-                                      : fwd_dispatch_n<1, 1>(p, N, stream, lent);
+        e = desc->out_dtype == MB_F32 ? fwd_dispatch_n<1, 0>(p, f, N, stream, lent)
+                                      : fwd_dispatch_n<1, 1>(p, f, N, stream, lent);
     return e == hipSuccess ? MB_OK : MB_ERR_HIP;
 }
 

@@ -46,6 +46,7 @@
 #include <hip/hip_runtime.h>
 
 #include "device_math.hpp"
+#include "fwd_plan.hpp"
 #include "scan_params.hpp"
 #include "scan_tiled.hpp"
 
@@ -475,54 +476,21 @@ __global__ __launch_bounds__(kMaxWaves * 64) void scan_fwd_ring(ScanParams p, Ri
 
 // ---- host side ------------------------------------------------------------------
 
-// Waves per chain.  4 (one per SIMD) for most: measured with 1, 2, 4 and 8, bf16 in and
-// fp32 out, (4, 3584, 8192) took 546, 541, 492 and 559 us, (4, 2048, 8192) 410, 306, 292 and
-// 316, (1, 4608, 65536) 3123, 2296, 1583 and 1999, (1, 3584, 1013) 56, 34, 24 and 25: fewer
-// waves leave SIMDs unevenly filled or idle, more make the chain's hand-overs its pace.
-// 8 with at most one chain per CU ((1, 2048, 8192): 115 us with 4, 109 with 8).
-// With more than 4 chains per CU the waves of short sequences come in several rounds, where
-// each wave's start-up counts: 2 up to 16 slices ((4, 3584, 192): 16.7, 16.5, 18.1 and 25.8
-// us with 1, 2, 4 and 8; (4, 4608, 256): 28.0, 25.4, 25.4 and 36.0), 1 up to 4 slices
-// ((16, 3584, 48): 17.1, 19.6, 25.1 and 41.0).
-inline uint32_t waves_per_chain_log2(int64_t chains, int64_t slices) {
-    const int64_t cus = tiled::device_cus();
-    uint32_t lw = chains <= cus ? 3 : 2;
-    if (chains > 4 * cus && slices <= 16) lw = slices <= 4 ? 0 : 1;
-    while (lw > 0 && (int64_t(1) << lw) > slices) --lw;
-    return lw;
-}
-
-// The time segments the forward takes for p (1: none), their length and the pre-pass
-// pieces per segment.  The pre-pass repeats the exponentials of all segments but the last,
-// so segments are taken only with fewer than 3/4 of a chain per CU, and then about 4 CUs'
-// worth of chains (4 workgroups each): (1, 1024, 8192), 128 chains, took 107 us unsegmented,
-// 76 in 4, 67 in 8 and 75 in 16 segments; (1, 2048, 8192), 256 chains, 107 unsegmented
-// against 116 or more; (1, 1536, 2048), 192 chains, 31 against 35.  A short sequence is
-// done before the pre-pass pays: (1, 1024, 1024) took 14 us unsegmented, 31 in 4 segments.
-inline int64_t segments(const ScanParams &p, int64_t *seg_len, int64_t *pieces) {
-    const int64_t n_cg = (p.dim + kCh - 1) / kCh, cus = tiled::device_cus();
-    *seg_len = p.seqlen;
-    *pieces = 1;
-    return p.seqlen >= 3072 ? tiled::choose_segments(n_cg * p.batch, p.seqlen, 2 * cus, 4 * cus, seg_len, pieces) : 1;
-}
-
 template <int IN, int OUT, bool GATE, bool SP>
-hipError_t fwd_ring_sp(ScanParams &p, void *stream, float *lent) {
+hipError_t fwd_ring_sp(ScanParams &p, const plan::Fwd &f, void *stream, float *lent) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     RingParams g{};
     g.n_cg = (uint32_t)((p.dim + kCh - 1) / kCh);
-    int64_t seg_len = p.seqlen, pieces = 1;
-    const int64_t nseg = segments(p, &seg_len, &pieces);
     float *carry = nullptr;
     hipError_t e;
-    if (nseg > 1) {
+    if (f.nseg > 1) {
         if (lent) {
             carry = lent;
         } else {
-            e = hipMallocAsync(reinterpret_cast<void **>(&carry), tiled::fwd_carry_bytes(p, nseg, pieces), st);
+            e = hipMallocAsync(reinterpret_cast<void **>(&carry), plan::carry_bytes(p.batch * p.dim, f), st);
             if (e != hipSuccess) return e;
         }
-        int64_t piece_len = seg_len / pieces, npieces = pieces * (nseg - 1);
+        int64_t piece_len = f.seg_len / f.pieces, npieces = f.pieces * (f.nseg - 1);
         const int64_t waves = (int64_t)g.n_cg * p.batch * npieces;
         const int64_t blocks = (waves + tiled::kWavesPerGroup - 1) / tiled::kWavesPerGroup;
         void *args[] = {&p, &piece_len, &npieces, &carry};
@@ -533,32 +501,29 @@ hipError_t fwd_ring_sp(ScanParams &p, void *stream, float *lent) {
             return e;
         }
     }
-    const int64_t chains = (int64_t)g.n_cg * p.batch * nseg;
-    const int64_t slices = (seg_len + kS - 1) / kS;
-    g.nseg = (uint32_t)nseg;
-    g.seg_len = (uint32_t)seg_len;
-    g.pieces = (uint32_t)pieces;
-    g.chains = (uint32_t)chains;
-    g.log_w = waves_per_chain_log2(chains, slices);
+    g.nseg = (uint32_t)f.nseg;
+    g.seg_len = (uint32_t)f.seg_len;
+    g.pieces = (uint32_t)f.pieces;
+    g.chains = (uint32_t)f.chains;
+    g.log_w = f.log_w;
     g.carry = carry;
-    const int w = 1 << g.log_w, wg = w > 4 ? w : 4, per_wg = wg / w;
-    const dim3 grid((unsigned)((chains + per_wg - 1) / per_wg)), block(64 * wg);
     void *args[] = {&p, &g};
     const void *fn = p.npos > 0 ? reinterpret_cast<const void *>(&scan_fwd_ring<IN, OUT, GATE, SP, kPositions>)
                      : p.ck     ? reinterpret_cast<const void *>(&scan_fwd_ring<IN, OUT, GATE, SP, kCheckpoints>)
                                 : reinterpret_cast<const void *>(&scan_fwd_ring<IN, OUT, GATE, SP, kPlain>);
-    e = hipLaunchKernel(fn, grid, block, args, sizeof(WaveSmem) * wg + 4 * kMaxWaves, st);
+    e = hipLaunchKernel(fn, dim3((unsigned)f.workgroups), dim3(f.threads), args,
+                        sizeof(WaveSmem) * (f.threads / 64) + 4 * kMaxWaves, st);
     if (carry && !lent) {
-        const hipError_t f = hipFreeAsync(carry, st);
-        if (e == hipSuccess) e = f;
+        const hipError_t fr = hipFreeAsync(carry, st);
+        if (e == hipSuccess) e = fr;
     }
     return e;
 }
 
 template <int IN, int OUT, bool GATE>
-hipError_t fwd_ring(ScanParams &p, void *stream, float *lent) {
-    return p.delta_softplus ? fwd_ring_sp<IN, OUT, GATE, true>(p, stream, lent)
-                            : fwd_ring_sp<IN, OUT, GATE, false>(p, stream, lent);
+hipError_t fwd_ring(ScanParams &p, const plan::Fwd &f, void *stream, float *lent) {
+    return p.delta_softplus ? fwd_ring_sp<IN, OUT, GATE, true>(p, f, stream, lent)
+                            : fwd_ring_sp<IN, OUT, GATE, false>(p, f, stream, lent);
 }
 
 }  // namespace ring

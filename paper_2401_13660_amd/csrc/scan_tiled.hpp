@@ -518,38 +518,6 @@ __global__ __launch_bounds__(kThreads) void scan_seg_agg(ScanParams p, int64_t p
 
 // ---- host side: launch configuration -------------------------------------
 
-// Time segments of the forward.  With fewer than 3/8 `resident` waves (8 channels of one
-// batch element each, for the whole sequence) the sequence is cut into segments (each a
-// multiple of 32 bytes, at least 256).  A pre-pass computes each segment's aggregate from
-// a zero state; the scan of segment s then starts from h0 folded with the aggregates of
-// segments 0 .. s-1.  The count is the largest that gives at most 2 `resident` waves.
-// The caller's `resident` says what it fills the chip with; the ring kernel's is 2 per
-// CU (see ring::segments).
-// The pre-pass cuts each segment into `pieces` (1 or 2) equal pieces, one wave
-// per piece and 8 channels.  A SIMD takes as long as its largest number of
-// waves times the piece length, so 2 pieces are taken where that is shorter:
-// ceil(2 w / simds) / 2 below ceil(w / simds), for the w waves of whole
-// segments.  That takes 2 pieces only up to 7 waves per SIMD, as many as fit
-// with bf16 inputs (70 VGPRs), so those waves are all resident at once.
-inline int64_t choose_segments(int64_t waves_base, int64_t L, int64_t resident, int64_t simds, int64_t *seg_len,
-                               int64_t *pieces) {
-    int64_t nseg = 1;
-    if (waves_base > 0 && waves_base * 8 < resident * 3) nseg = 2 * resident / waves_base;
-    const int64_t max_seg = L / 256;
-    if (nseg > max_seg) nseg = max_seg;
-    if (nseg < 1) nseg = 1;
-    int64_t m = 1;
-    if (nseg > 1) {
-        const int64_t w = waves_base * (nseg - 1);
-        if ((2 * w + simds - 1) / simds < 2 * ((w + simds - 1) / simds)) m = 2;
-    }
-    int64_t len = (L + nseg - 1) / nseg;
-    len = (len + 32 * m - 1) / (32 * m) * (32 * m);     // pieces of a multiple of 32 timesteps
-    *seg_len = len;
-    *pieces = m;
-    return (L + len - 1) / len;
-}
-
 // Compute units of the current device; 256 (MI355X) if the runtime cannot say.
 inline int64_t device_cus() {
     int dev = 0, cus = 0;
@@ -561,12 +529,6 @@ inline int64_t device_cus() {
 
 // Waves resident at once on the current device at 2 per SIMD.
 inline int64_t resident_waves() { return 8 * device_cus(); }
-
-// Device bytes of the segment carry: the aggregates of the pieces of segments
-// 0 .. nseg-2, then the copy of h0 (rows x 16 states x 2 floats per plane).
-inline size_t fwd_carry_bytes(const ScanParams &p, int64_t nseg, int64_t pieces) {
-    return nseg > 1 ? (size_t)(pieces * (nseg - 1) + 1) * (size_t)(p.batch * p.dim) * kN * 2 * sizeof(float) : 0;
-}
 
 template <int IN, int OUT, bool GATE, bool SP>
 hipError_t fwd_short_sp(ScanParams &p, void *stream) {

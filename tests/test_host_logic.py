@@ -1,95 +1,63 @@
 """Host-side launch logic of the library, run on the CPU.
 
-The forward cuts the sequence into time segments when the (batch, channel)
-rows are too few to fill the chip: the count is the largest that fills the
-resident waves at most twice over, for fewer than 3/8 of them per segment;
-segments are at least 256 bytes and a multiple of 32.  The segment pre-pass
-cuts each segment into 2 pieces (then segments are a multiple of 64) where
-that shortens its busiest SIMD's work: ceil(2 w / simds) / 2 below
-ceil(w / simds) for its w one-piece waves.  A small host program
-built from the library's own header prints its choice; the expectations come
-from that rule, written out here, and from a few cases worked by hand.
+The library's own rules (csrc/fwd_plan.hpp) compiled into a small host program, on the 256
+compute units of an MI355X.
 """
-import math
-import os
-import shutil
-import subprocess
-
 import pytest
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-CSRC = os.path.join(ROOT, "paper_2401_13660_amd", "csrc")
-HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+from plan_util import have_compiler, plan, plans
 
-pytestmark = pytest.mark.skipif(not os.path.exists(HIPCC) and shutil.which("hipcc") is None,
-                                reason="needs hipcc")
+pytestmark = pytest.mark.skipif(not have_compiler(), reason="needs a C++ compiler")
 
-
-@pytest.fixture(scope="module")
-def segments_exe(tmp_path_factory):
-    exe = tmp_path_factory.mktemp("host") / "segments"
-    subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-I", CSRC,
-                    os.path.join(ROOT, "tests", "host", "segments_main.cpp"), "-o", str(exe)],
-                   check=True, capture_output=True, text=True)
-    return str(exe)
+U32 = 2 ** 32 - 1        # HIP's limit on workgroups x threads along a grid dimension
 
 
-def _rule(wb: int, L: int, resident: int, simds: int):
-    n = 2 * resident // wb if wb * 8 < resident * 3 else 1
+# batch x ceil(dim / 8) chains round the bounds of a launch with 4, 2 and 1 waves each, at a
+# length that takes 4, 2 or 1 wave where they fit
+@pytest.mark.parametrize("L", [1, 33, 272])
+@pytest.mark.parametrize("chains", [2 ** 24 - 1, 2 ** 24, 2 ** 25 - 1, 2 ** 25, 2 ** 26 - 4, 2 ** 26, 2 ** 28])
+def test_every_problem_fits_its_launch(L, chains):
+    p = plan((chains, 8, L))
+    assert p.workgroups * p.threads <= U32, p
+    if p.kernel == "ring":
+        assert p.workgroups * (p.threads // 64) >= chains * p.waves
+    else:
+        assert p.kernel == "row" and p.workgroups * p.threads >= 8 * chains
+    # one wave per chain fits below 2^26 chains
+    assert (p.kernel == "ring") == (chains < 2 ** 26)
+    aligned16 = plan((1, 8 * chains, 16))
+    assert aligned16.workgroups * aligned16.threads <= U32, aligned16
+
+
+def _rule(chains: int, L: int):
+    """nseg, seg_len, pieces: the most segments that make at most 1,024 chains, of at least
+    256 timesteps; 2 pre-pass pieces where that shortens the busiest SIMD's work."""
+    n = 1024 // chains if chains * 8 < 512 * 3 and L >= 3072 else 1
     n = max(1, min(n, L // 256))
-    m = 1
-    if n > 1:
-        w = wb * (n - 1)
-        if -(-2 * w // simds) < 2 * -(-w // simds):
-            m = 2
-    seg = -(-L // n)
-    seg = -(-seg // (32 * m)) * (32 * m)
+    if n == 1:
+        return 1, None, 1
+    w = chains * (n - 1)
+    m = 2 if -(-2 * w // 1024) < 2 * -(-w // 1024) else 1
+    seg = -(-(-(-L // n)) // (32 * m)) * (32 * m)
     return -(-L // seg), seg, m
 
 
-def _run(exe, cases):
-    out = subprocess.run([exe], input="".join(f"{w} {L} {r} {s}\n" for w, L, r, s in cases), check=True,
-                         capture_output=True, text=True).stdout.split("\n")
-    return [tuple(int(v) for v in line.split()) for line in out if line.strip()]
+def test_segments_follow_the_rule():
+    shapes = [(1, 8 * c, L) for c in (1, 3, 8, 100, 128, 191, 192, 255, 256, 448, 576, 1792)
+              for L in (16, 256, 1008, 3071, 3072, 4096, 8190, 8192, 65536)]
+    for (nb, dim, L), p in zip(shapes, plans(shapes, aligned=False)):
+        n, seg, m = _rule(dim // 8, L)
+        assert (p.nseg, p.pieces) == (n, m), (dim, L, p)
+        if n > 1:
+            assert p.seg_len == seg and seg % (32 * m) == 0 and seg >= 256
+            assert (n - 1) * seg < L <= n * seg
+            assert 0 < p.carry <= 8 << 20                # the allocation-free call's array
 
 
-# (waves_base, L, resident, simds) -> (segments, segment length, pre-pass pieces), worked by hand
-HAND = [
-    ((576, 65536, 2048, 1024), (7, 9408, 2)),   # 1.6B layer, batch 1: 3456 pre-pass waves are 3.375
-                                                # per SIMD (4 on some), 6912 are 6.75 (7): 7/2 < 4, so
-                                                # 2 pieces; ceil(65536/7) = 9363 -> 9408 (64 | 9408)
-    ((1792, 8192, 2048, 1024), (1, 8192, 1)),   # 972M layer: enough rows
-    ((1024, 8192, 2048, 1024), (1, 8192, 1)),   # 353M layer: at the threshold's far side
-    ((448, 8192, 2048, 1024), (9, 960, 2)),     # 972M shape at batch 1: 4096 // 448 = 9; 3584 waves:
-                                                # ceil(7)/2 < ceil(3.5); ceil(8192/9) = 911 -> 960
-    ((8, 4096, 2048, 1024), (16, 256, 2)),      # few rows: capped at 256-byte segments, 120 waves
-    ((1, 4112, 2048, 1024), (13, 320, 2)),      # ceil(4112/16) = 257 -> 320 bytes, so 13 segments
-    ((1, 640, 2048, 1024), (2, 320, 2)),
-    ((767, 8192, 2048, 1024), (5, 1664, 1)),    # just below 3/8 of the resident waves; 3068 waves:
-                                                # ceil(5.99) = 6 = 2 ceil(2.996), so one piece
-    ((768, 8192, 2048, 1024), (1, 8192, 1)),    # at 3/8: no segments
-    ((750, 1296, 2048, 1024), (5, 288, 1)),     # 4096 // 750 = 5 = 1296 // 256; 3000 waves: ceil(5.86)
-                                                # = 6 = 2 ceil(2.93), one piece; ceil(1296/5) = 260 -> 288
-    ((576, 65536, 512, 256), (1, 65536, 1)),    # a device with 64 CUs: 576 waves fill it
-    ((1, 16, 2048, 1024), (1, 32, 1)),          # one segment, its length rounded up to 32 (the launcher
-                                                # does not cut sequences below 512 bytes at all)
-]
-
-
-def test_segment_counts_worked_by_hand(segments_exe):
-    got = _run(segments_exe, [c for c, _ in HAND])
-    assert got == [e for _, e in HAND]
-
-
-def test_segment_counts_follow_the_rule(segments_exe):
-    cases = [(wb, L, r, r // 2) for r in (512, 2048, 4096)
-             for wb in (1, 3, 8, 100, 255, 256, 448, 576, 700, 1000, 1535, 1536, 5000)
-             for L in (16, 256, 512, 528, 1008, 4096, 8192, 65536)]
-    got = _run(segments_exe, cases)
-    for (wb, L, r, s), g in zip(cases, got):
-        assert g == _rule(wb, L, r, s), (wb, L, r, s, g)
-        n, seg, m = g
-        assert seg % (32 * m) == 0 or n == 1
-        assert (n - 1) * seg < L <= n * seg
-        assert n == 1 or seg >= 256
-        assert m in (1, 2) and (n > 1 or m == 1)
+def test_waves_per_chain():
+    """8 up to one chain per compute unit, 4 above; with more than 4 per unit 2 up to 16
+    slices of 16 timesteps and 1 up to 4; never more than there are slices."""
+    shapes = {(256, 2048): 8, (257, 2048): 4, (1024, 16 * 16): 4, (1025, 16 * 16): 2, (1025, 16 * 17): 4,
+              (1025, 16 * 5): 2, (1025, 16 * 4): 1, (1024, 16 * 4): 4, (256, 48): 2, (256, 33): 2, (256, 17): 2, (256, 9): 1}
+    got = plans([(1, 8 * c, L) for c, L in shapes], aligned=False)
+    assert [p.waves for p in got] == list(shapes.values())
