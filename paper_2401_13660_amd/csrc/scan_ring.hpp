@@ -191,7 +191,12 @@ __global__ __launch_bounds__(kMaxWaves * 64) void scan_fwd_ring(ScanParams p, Ri
     using Raw = Pair<IN>;
     struct Slot { Raw u, dl, z, B0, B1, C0, C1; } sl;
     // Loads never branch: past the last full slice a wave reads its first again (never
-    // consumed).
+    // consumed).  A wave's next slice is asked for as soon as the last one's registers are
+    // free, except where the 128 VGPRs do not hold it beside the exponentials (14 registers
+    // of fp32, or the state and positions to record): then after them, before the wait for
+    // the state.  Spilled instead, (4, 3584, 2048) fp32 took 242 us, this way 156; bf16 with
+    // checkpoints (4, 3584, 8192) 577 and 564.
+    constexpr bool kLateLoads = IN == 0 || REC != kPlain;
     const uint32_t oa = act_row + 2 * q, ob = bc_row + 2 * j;
     auto issue_loads = [&](uint32_t i) {
         const uint32_t t0 = t_begin + (i < nfull ? i : (uint32_t)r) * kS;
@@ -277,7 +282,7 @@ __global__ __launch_bounds__(kMaxWaves * 64) void scan_fwd_ring(ScanParams p, Ri
         sm.b2[j][q] = f32x4{sl.B0.get(0), sl.B1.get(0), sl.B0.get(1), sl.B1.get(1)};
         sm.c2[j][q] = f32x4{sl.C0.get(0), sl.C1.get(0), sl.C0.get(1), sl.C1.get(1)};
         wave_sync();
-        issue_loads(s + W);                              // the wave's next slice
+        if constexpr (!kLateLoads) issue_loads(s + W);   // the wave's next slice
 
         // ---- E: abar and bx of all 16 timesteps
         float ab[kS][2], hx[kS][2];
@@ -334,6 +339,8 @@ __global__ __launch_bounds__(kMaxWaves * 64) void scan_fwd_ring(ScanParams p, Ri
 #pragma unroll
         for (int t = 0; t < kS; ++t)
             asm volatile("" : "+v"(ab[t][0]), "+v"(ab[t][1]), "+v"(hx[t][0]), "+v"(hx[t][1]));
+
+        if constexpr (kLateLoads) issue_loads(s + W);
 
         // ---- H: the state before the slice, the chain, the hand-over
         take_state(s);
