@@ -89,3 +89,25 @@ def test_positions_in_every_part(L):
     assert np.isnan(got[4]).all()
     assert rel_err(got[:4], ref[:4]) <= TOL_H
     assert np.array_equal(got[2, 0], h0_last[0].cpu().numpy())
+
+
+@pytest.mark.parametrize("L", [7, 16, 83, 4099])
+def test_more_positions_than_lanes(L):
+    """130 positions per batch element, valid ones, -1 and ones past both ends among the first
+    64, the second and the last 2: all looked for 64 at a time by the ring kernel (and by the
+    16-timestep kernel at L = 16), in full slices, in the timesteps after them, in segments."""
+    import paper_2401_13660_amd as mb
+    from test_gpu_positions import check_states
+    inp = make_inputs(2, 11, L, 16, seed=9, with_h0=True)
+    rng = np.random.default_rng(L)
+    pos = rng.integers(0, L, (130, 2)).astype(np.int32)
+    for k in (0, 63, 64, 127, 128, 129):
+        pos[k] = rng.permutation([L - 1, -1])
+    for k, p in ((5, L), (62, -2), (65, -2), (100, 2 ** 31 - 1), (126, -2 ** 31)):
+        pos[k, k % 2] = p
+    t = to_device(inp)
+    announce(f"ring, 130 positions, L={L}")
+    _, h, h_at = mb.scan_fwd(t["u"], t["delta"], t["A"], t["B"], t["C"], D=t["Dskip"], dt_bias=t["dt_bias"], z=t["z"],
+                             h0=t["h0"], positions=torch.from_numpy(pos).to("cuda:0"), return_last_state=True)
+    torch.cuda.synchronize()
+    check_states(inp, pos, h_at, h)
