@@ -50,14 +50,24 @@ inline int64_t ring_workgroups(int64_t chains, uint32_t log_w) {
 // 316, (1, 4608, 65536) 3123, 2296, 1583 and 1999, (1, 3584, 1013) 56, 34, 24 and 25: fewer
 // waves leave SIMDs unevenly filled or idle, more make the chain's hand-overs its pace.
 // 8 with at most one chain per CU ((1, 2048, 8192): 115 us with 4, 109 with 8).
-// With more than 4 chains per CU the waves of short sequences come in several rounds, where
-// each wave's start-up counts: 2 up to 16 slices ((4, 3584, 192): 16.7, 16.5, 18.1 and 25.8
-// us with 1, 2, 4 and 8; (4, 4608, 256): 28.0, 25.4, 25.4 and 36.0), 1 up to 4 slices
-// ((16, 3584, 48): 17.1, 19.6, 25.1 and 41.0).
+// The waves of short sequences come in several rounds where chains are many, and each
+// wave's start-up counts.  Measured with 1, 2, 4 waves, in us:
+//   from 3 chains per CU    2 up to 8 slices     (2, 3584, 96)     8.5,  7.8,  8.3
+//                           4 above              (2, 3584, 192)   13.0, 11.3, 10.9
+//   from 4 chains per CU    1 up to 4 slices     (16, 3584, 48)   17.1, 19.6, 25.1
+//                           2 up to 16           (2, 4608, 256)   20.0, 17.0, 16.3
+//   from 7 chains per CU    1 up to 8            (4, 3584, 128)   12.2, 12.5, 14.4
+//   from 8 chains per CU    2 up to 32           (8, 3584, 512)   63.4, 59.5, 60.4
+//                           4 above              (8, 3584, 2048)   280,  243,  237
+//   from 16 chains per CU   1 up to 16           (16, 3584, 256)  58.1, 59.6, 65.4
+//                           2 up to 32           (32, 3584, 272)   151,  150,  162
 // Fewer where the launch would not fit a grid dimension otherwise.
 inline uint32_t waves_per_chain_log2(int64_t chains, int64_t slices, int64_t cus) {
     uint32_t lw = chains <= cus ? 3 : 2;
-    if (chains > 4 * cus && slices <= 16) lw = slices <= 4 ? 0 : 1;
+    if (chains > 4 * cus && slices <= 16)
+        lw = slices <= 4 || (slices <= 8 && chains >= 7 * cus) || chains > 16 * cus ? 0 : 1;
+    else if ((chains > 3 * cus && slices <= 8) || (chains > 8 * cus && slices <= 32))
+        lw = 1;
     while (lw > 0 && ((int64_t(1) << lw) > slices || !launch_fits(ring_workgroups(chains, lw), ring_threads(lw)))) --lw;
     return lw;
 }

@@ -55,9 +55,12 @@ def test_segments_follow_the_rule():
 
 
 def test_waves_per_chain():
-    """8 up to one chain per compute unit, 4 above; with more than 4 per unit 2 up to 16
-    slices of 16 timesteps and 1 up to 4; never more than there are slices."""
-    shapes = {(256, 2048): 8, (257, 2048): 4, (1024, 16 * 16): 4, (1025, 16 * 16): 2, (1025, 16 * 17): 4,
-              (1025, 16 * 5): 2, (1025, 16 * 4): 1, (1024, 16 * 4): 4, (256, 48): 2, (256, 33): 2, (256, 17): 2, (256, 9): 1}
-    got = plans([(1, 8 * c, L) for c, L in shapes], aligned=False)
-    assert [p.waves for p in got] == list(shapes.values())
+    """8 up to one chain per compute unit, 4 above; fewer for short sequences of many chains;
+    never more than there are slices of 16 timesteps."""
+    want = {(256, 2048): 8, (257, 2048): 4, (256, 48): 2, (256, 33): 2, (256, 17): 2, (256, 9): 1,
+            (768, 128): 4, (769, 128): 2, (769, 129): 4, (1024, 64): 2, (1024, 129): 4,
+            (1025, 64): 1, (1025, 65): 2, (1025, 256): 2, (1025, 257): 4,
+            (1791, 128): 2, (1792, 128): 1, (1792, 129): 2, (2048, 257): 4,
+            (2049, 257): 2, (2049, 512): 2, (2049, 513): 4, (4096, 256): 2, (4097, 256): 1, (4097, 257): 2}
+    got = plans([(1, 8 * c, L) for c, L in want], aligned=False)
+    assert {k: p.waves for k, p in zip(want, got)} == want
