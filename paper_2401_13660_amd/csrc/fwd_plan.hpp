@@ -72,49 +72,46 @@ inline uint32_t waves_per_chain_log2(int64_t chains, int64_t slices, int64_t cus
     return lw;
 }
 
-// Time segments of the forward.  With fewer than 3/8 `resident` waves (8 channels of one
-// batch element each, for the whole sequence) the sequence is cut into segments (each a
-// multiple of 32 bytes, at least 256).  A pre-pass computes each segment's aggregate from
-// a zero state; the scan of segment s then starts from h0 folded with the aggregates of
-// segments 0 .. s-1.  The count is the largest that gives at most 2 `resident` waves.
-// The caller's `resident` says what it fills the chip with; the ring kernel's is 2 per
-// CU (see segments).
-// The pre-pass cuts each segment into `pieces` (1 or 2) equal pieces, one wave
-// per piece and 8 channels.  A SIMD takes as long as its largest number of
-// waves times the piece length, so 2 pieces are taken where that is shorter:
-// ceil(2 w / simds) / 2 below ceil(w / simds), for the w waves of whole
-// segments.  That takes 2 pieces only up to 7 waves per SIMD, as many as fit
-// with bf16 inputs (70 VGPRs), so those waves are all resident at once.
-inline int64_t choose_segments(int64_t waves_base, int64_t L, int64_t resident, int64_t simds, int64_t *seg_len,
-                               int64_t *pieces) {
-    int64_t nseg = 1;
-    if (waves_base > 0 && waves_base * 8 < resident * 3) nseg = 2 * resident / waves_base;
-    const int64_t max_seg = L / 256;
-    if (nseg > max_seg) nseg = max_seg;
-    if (nseg < 1) nseg = 1;
-    int64_t m = 1;
-    if (nseg > 1) {
-        const int64_t w = waves_base * (nseg - 1);
-        if ((2 * w + simds - 1) / simds < 2 * ((w + simds - 1) / simds)) m = 2;
-    }
-    int64_t len = (L + nseg - 1) / nseg;
-    len = (len + 32 * m - 1) / (32 * m) * (32 * m);     // pieces of a multiple of 32 timesteps
+// Time segments of the forward (1: none), their length and the pre-pass pieces per segment.
+// A pre-pass computes each segment's aggregate from a zero state; the scan of segment s then
+// starts from h0 folded with the aggregates of segments 0 .. s-1.  The pre-pass repeats the
+// exponentials of all segments but the last, so the sequence is cut only where its chains
+// leave the chip unevenly or hardly filled (bf16 in, us unsegmented and cut):
+// - fewer than 7/8 of a chain per CU, into about 4 CUs' worth of chains, the fewer the
+//   earlier: up to half a chain per CU from 2048 timesteps ((1, 1024, 2048), 128 chains, 30
+//   and 26; (1, 64, 2048) 30 and 23, (1, 64, 1536) 23 either way); up to 5/8 from 3072 ((1,
+//   1280, 3056), 160 chains, 43 and 40, (1, 1280, 2048) 30 either way); below 3/4 from 4096
+//   ((1, 1528, 6000), 191 chains, 80 and 75, (1, 1528, 3056) 43 and 45); below 7/8 from 16384
+//   ((1, 1536, 16384), 192 chains, 207 and 164, (1, 1792, 16384), 224 chains, 208 and 210).
+// - just over one chain per CU, where a few CUs take two and set the time, from 8192
+//   timesteps into 8: (1, 2112, 8192), 264 chains, 146 and 129, (1, 2304, 32768), 288 chains,
+//   571 and 492; (1, 2432, 16384), 304 chains, 287 and 307.
+// Segments have at least 256 timesteps and number at most 128, for the fold over the earlier
+// ones is serial: (1, 8, 65536) took 131 us in 256 segments of 2 pieces and 58 in 128.
+// One wave of the pre-pass runs per piece and 8 channels; alone on its SIMD it waits on its
+// chain of dependent operations.  A segment is cut into 2 or 4 pieces while that makes at
+// most 4 waves per SIMD, of at least 512 and 768 timesteps: (1, 1024, 32768), 8 segments in
+// 1, 2 and 4 pieces, 271, 249 and 248; (1, 1536, 16384), 5 segments in 2 and 4, 189 and 164;
+// (1, 512, 8192), 16 segments of 512 timesteps in 1 and 2, 44 and 47; (1, 512, 32768), 16 of
+// 2048 in 2 and 4, 125 and 128.
+inline int64_t segments(int64_t chains, int64_t L, int64_t cus, int64_t *seg_len, int64_t *pieces) {
+    int64_t n = 1, m = 1;
+    const int64_t least_L = chains * 8 <= cus * 4 ? 2048 : chains * 8 <= cus * 5 ? 3072
+                            : chains * 8 < cus * 6 ? 4096 : 16384;
+    if (chains * 8 < cus * 7 && L >= least_L) n = 4 * cus / chains;
+    if (chains > cus && chains * 8 <= cus * 9 && L >= 8192) n = 8;
+    if (n > L / 256) n = L / 256;
+    if (n > 128) n = 128;
+    *seg_len = L;
+    *pieces = 1;
+    if (n <= 1) return 1;
+    const int64_t least = (L + n - 1) / n;
+    while (m < 4 && 2 * m * chains * (n - 1) <= 16 * cus && least >= (m == 1 ? 1024 : 3072)) m *= 2;
+    const int64_t unit = 32 * m;                        // pieces of a multiple of 32 timesteps
+    const int64_t len = (least + unit - 1) / unit * unit;
     *seg_len = len;
     *pieces = m;
     return (L + len - 1) / len;
-}
-
-// The time segments the forward takes (1: none), their length and the pre-pass
-// pieces per segment.  The pre-pass repeats the exponentials of all segments but the last,
-// so segments are taken only with fewer than 3/4 of a chain per CU, and then about 4 CUs'
-// worth of chains (4 workgroups each): (1, 1024, 8192), 128 chains, took 107 us unsegmented,
-// 76 in 4, 67 in 8 and 75 in 16 segments; (1, 2048, 8192), 256 chains, 107 unsegmented
-// against 116 or more; (1, 1536, 2048), 192 chains, 31 against 35.  A short sequence is
-// done before the pre-pass pays: (1, 1024, 1024) took 14 us unsegmented, 31 in 4 segments.
-inline int64_t segments(int64_t chains, int64_t L, int64_t cus, int64_t *seg_len, int64_t *pieces) {
-    *seg_len = L;
-    *pieces = 1;
-    return L >= 3072 ? choose_segments(chains, L, 2 * cus, 4 * cus, seg_len, pieces) : 1;
 }
 
 // The plan of a scan with at least one row and one timestep; cus_of says how many compute

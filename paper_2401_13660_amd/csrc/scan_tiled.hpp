@@ -340,10 +340,8 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_short(ScanParams p) {
 // every later segment by the fold P h + H.  The pairs (P, H) go to
 // carry[((piece * rows + row) * 16 + n) * 2 + {0, 1}].
 //
-// Pieces smaller than the scan's segments balance the pass: one wave per piece
-// and 8 channels, and with one piece per segment the 1.6B layer's 3,456 waves
-// leave 4 on some SIMDs and 3 on others, while 6,912 half-length pieces make 6.75
-// per SIMD against at most 7.
+// Pieces smaller than the scan's segments give a SIMD several waves of this pass, which
+// fill each other's waits (plan::segments has the rule and what it measured).
 //
 // A walk from the segment's end that stops once the running product of abar is
 // exactly zero in fp32 gives the same (P, H) with fewer timesteps, but with the

@@ -30,28 +30,46 @@ def test_every_problem_fits_its_launch(L, chains):
 
 
 def _rule(chains: int, L: int):
-    """nseg, seg_len, pieces: the most segments that make at most 1,024 chains, of at least
-    256 timesteps; 2 pre-pass pieces where that shortens the busiest SIMD's work."""
-    n = 1024 // chains if chains * 8 < 512 * 3 and L >= 3072 else 1
-    n = max(1, min(n, L // 256))
-    if n == 1:
+    """segments, their length, pre-pass pieces."""
+    n = 1
+    if chains < 224 and L >= (2048 if chains <= 128 else 3072 if chains <= 160 else 4096 if chains < 192 else 16384):
+        n = 1024 // chains
+    if 256 < chains <= 288 and L >= 8192:
+        n = 8
+    n = min(n, L // 256, 128)
+    if n <= 1:
         return 1, None, 1
-    w = chains * (n - 1)
-    m = 2 if -(-2 * w // 1024) < 2 * -(-w // 1024) else 1
-    seg = -(-(-(-L // n)) // (32 * m)) * (32 * m)
+    least = -(-L // n)
+    m = 1
+    if least >= 1024 and 2 * chains * (n - 1) <= 4096:
+        m = 4 if least >= 3072 and 4 * chains * (n - 1) <= 4096 else 2
+    seg = -(-least // (32 * m)) * (32 * m)
     return -(-L // seg), seg, m
 
 
 def test_segments_follow_the_rule():
-    shapes = [(1, 8 * c, L) for c in (1, 3, 8, 100, 128, 191, 192, 255, 256, 448, 576, 1792)
-              for L in (16, 256, 1008, 3071, 3072, 4096, 8190, 8192, 65536)]
+    shapes = [(1, 8 * c, L) for c in (1, 3, 8, 31, 100, 128, 129, 160, 161, 191, 192, 223, 224, 255, 256, 257, 264, 288, 289, 448,
+                                      576, 1792)
+              for L in (16, 256, 1008, 2047, 2048, 3071, 4095, 4096, 8190, 8192, 20480, 65536, 2 ** 24)]
     for (nb, dim, L), p in zip(shapes, plans(shapes, aligned=False)):
         n, seg, m = _rule(dim // 8, L)
         assert (p.nseg, p.pieces) == (n, m), (dim, L, p)
+        assert (p.carry > 0) == (n > 1)
         if n > 1:
             assert p.seg_len == seg and seg % (32 * m) == 0 and seg >= 256
             assert (n - 1) * seg < L <= n * seg
-            assert 0 < p.carry <= 8 << 20                # the allocation-free call's array
+    # worked by hand: segments, length, pieces
+    hand = {(1, 8, 65536): (128, 512, 1), (1, 64, 2048): (8, 256, 1), (1, 512, 16384): (16, 1024, 2),
+            (1, 1024, 32768): (8, 4096, 4), (1, 1528, 20480): (5, 4096, 4), (1, 1536, 16384): (5, 3328, 4), (1, 1528, 4095): (1, None, 1),
+            (1, 2304, 8192): (8, 1024, 2), (1, 2304, 8191): (1, None, 1), (1, 2312, 8192): (1, None, 1), (2, 24, 8192): (32, 256, 1)}
+    for (shape, want), p in zip(hand.items(), plans(list(hand), aligned=False)):
+        assert (p.nseg, None if p.nseg == 1 else p.seg_len, p.pieces) == want, (shape, p)
+
+
+def test_every_carry_fits_the_allocation_free_array():
+    """On 256 compute units no carry passes 4.5 MiB of the allocation-free call's 8 MiB."""
+    shapes = [(1, 8 * c, L) for c in range(1, 400) for L in (2048, 4096, 8192, 16384, 20480, 32768, 65536, 2 ** 24)]
+    assert 4 << 20 < max(p.carry for p in plans(shapes)) <= 4.5 * 2 ** 20
 
 
 def test_waves_per_chain():
