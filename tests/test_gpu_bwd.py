@@ -15,6 +15,7 @@ import torch
 import oracle
 from gpu_util import announce, dev_tensor, has_gpu
 from parity import rel_err
+from plan_util import plan
 from paper_2401_13660_amd.inputs import make_inputs, workload
 
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not has_gpu(), reason="needs a GPU")]
@@ -167,15 +168,14 @@ def _fwd_ckpt(t):
     return ck
 
 
-# (batch, dim, L): whole 32-step chunks with dead lanes; a trailing half chunk
-# (the time-split kernel: 39 plain waves); one row group cut into time segments
-# (the forward's pre-pass path); the 353M layer's width (the time-split kernel,
-# 1,024 plain waves), whose slices' entering states are the checkpoints.
-@pytest.mark.parametrize("shape", [(2, 196, 512), (3, 100, 208), (1, 64, 1024), (4, 2048, 1024)])
+# (batch, dim, L): dead lanes; an odd number of slices; few chains, uncut and cut into time
+# segments (whose waves start from a folded state); the 353M layer's width, 1,024 chains.
+@pytest.mark.parametrize("shape", [(2, 196, 512), (3, 100, 208), (1, 64, 1024), (1, 64, 4096), (4, 2048, 1024)])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_fwd_checkpoints_match_oracle_states(shape, dtype):
     """ck[k] is the state before timestep 16k: the oracle's state at position 16k - 1."""
     nb, dim, L = shape
+    assert (plan(shape, ckpt=True).nseg > 1) == (L == 4096)
     inp = make_inputs(nb, dim, L, 16, dtype=dtype, seed=67, with_h0=True)
     announce(f"forward checkpoints {shape} {dtype}")
     ck = _fwd_ckpt({k: dev_tensor(v) for k, v in inp.arrays().items()})
@@ -188,7 +188,7 @@ def test_fwd_checkpoints_match_oracle_states(shape, dtype):
     assert e <= 1e-4, f"checkpoints: relative error {e:.3e}"
 
 
-@pytest.mark.parametrize("shape,gated", [((2, 196, 512), True), ((1, 64, 1024), False), ((9, 1001, 64), True),
+@pytest.mark.parametrize("shape,gated", [((2, 196, 512), True), ((1, 64, 1024), False), ((1, 64, 4096), False), ((9, 1001, 64), True),
                                          ((12, 1024, 32), True), ((4, 2048, 256), True)])
 def test_bwd_from_forward_checkpoints(shape, gated):
     """The backward from the forward's checkpoints: oracle parity, and the same

@@ -10,6 +10,7 @@ import torch
 
 from gpu_util import announce, check_against_oracle, gpu_fwd, has_gpu, to_device
 from parity import TOL_Y_BF16_OUT
+from plan_util import plan
 from paper_2401_13660_amd.inputs import make_inputs, workload
 
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not has_gpu(), reason="needs a GPU")]
@@ -27,9 +28,8 @@ def test_tiny_config_full():
     run_case(inp)
 
 
-# Lengths that are multiples of 16 take the tiled kernel (1008 ends in a half
-# chunk); other lengths take the row-per-thread kernel.  dim 200 leaves dead
-# lanes in the last 8-channel group.
+# Whole slices of 16 timesteps, and a length that leaves 8 after them.  dim 200 fills its
+# 8-channel groups.
 @pytest.mark.parametrize("L", [1008, 1000])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("gated,with_h0", [(True, True), (False, False), (True, False)])
@@ -46,7 +46,7 @@ def test_edge_lengths(L):
     run_case(inp)
 
 
-# L = 16: one half chunk per wave, the half-size-table instantiation (the
+# L = 16: one slice per wave, the 16-timestep kernel (the
 # verify shape), across input and output types, with and without the gate and
 # softplus, and with dead lanes (dim 100).
 @pytest.mark.parametrize("dtype,gated,softplus,out", [("f32", True, True, torch.float32),
@@ -151,8 +151,8 @@ def test_h_last_may_alias_h0(L):
 
 
 # Shapes with few rows cut the sequence into time segments (a pre-pass of segment
-# aggregates, then one wave per segment): (1, 64, 4096) takes 16 segments,
-# (1, 61, 4112) 13 with dead lanes.  The waves of the last segment write h_last
+# aggregates, then a chain per segment): (1, 64, 4096), and (1, 61, 4112) with dead
+# lanes.  The waves of the last segment write h_last
 # while waves of earlier segments of the same rows may not have started, so the
 # scan must not read h0 itself there.  Each entry point that writes h_last is run
 # with h_last on top of h0.
@@ -162,6 +162,7 @@ def test_h_last_may_alias_h0_segmented(shape, entry):
     import paper_2401_13660_amd as mb
     import oracle
     nb, dim, L = shape
+    assert plan(shape, ckpt=entry == "ckpt").nseg > 1
     inp = make_inputs(nb, dim, L, 16, dtype="bf16", seed=21, with_h0=True)
     announce(f"h_last is h0, segmented {shape} via {entry}")
     t = to_device(inp)
@@ -184,39 +185,39 @@ def test_h_last_may_alias_h0_segmented(shape, entry):
         assert rel_err(hp, hp_ref) <= 1e-4
 
 
-# Shapes with at most one plain-kernel wave per SIMD and one time segment take the
-# kernel that cuts every chunk into two time slices inside the wave; the
-# checkpointing entry point always takes the plain kernel.  Both compute each
-# state by the same operations in the same order, so y and h_last must be equal
-# bit for bit (and both meet the oracle).
-@pytest.mark.parametrize("shape,dtype,out_dtype,gated,with_h0,softplus", [
-    ((4, 2048, 512), "bf16", torch.float32, True, False, True),       # 1024 plain waves
-    ((3, 100, 320), "f32", torch.bfloat16, False, True, False),       # dead lanes, half chunk
-    ((1, 8, 48), "bf16", torch.float32, True, True, True),            # one full and one half chunk
-    ((2, 36, 32), "f32", torch.float32, True, True, True),            # a single full chunk
-])
-def test_time_split_kernel_equals_plain(shape, dtype, out_dtype, gated, with_h0, softplus):
+# The number of waves that share a chain follows from the number of chains and the length; a
+# state comes from the same operations in the same order whatever it is, so copies of a batch
+# element have the same bits in every batch size, and storing checkpoints changes none.
+@pytest.mark.parametrize("dtype,out_dtype,gated,with_h0,softplus", [
+    ("bf16", torch.float32, True, False, True), ("f32", torch.bfloat16, False, True, False),
+    ("f32", torch.float32, True, True, True)])
+def test_same_bits_with_any_number_of_waves(dtype, out_dtype, gated, with_h0, softplus):
     import paper_2401_13660_amd as mb
-    nb, dim, L = shape
-    inp = make_inputs(nb, dim, L, 16, dtype=dtype, seed=31, gated=gated, with_h0=with_h0,
-                      with_bias=softplus)
+    dim, L = 2045, 256                                   # 256 chains, dead lanes
+    copies = {1: 8, 2: 4, 5: 2, 17: 1}                   # batch: waves per chain
+    assert {n: plan((n, dim, L)).waves for n in copies} == copies
+    inp = make_inputs(1, dim, L, 16, dtype=dtype, seed=31, gated=gated, with_h0=with_h0, with_bias=softplus)
     if not softplus:
         # used as given, Delta must stay positive (else abar > 1 and the state grows without bound)
         assert dtype == "f32"
         inp.delta = np.abs(inp.delta).astype(np.float32) * np.float32(0.05)
-    announce(f"time-split vs plain kernel {shape} {dtype} out={out_dtype} gated={gated} h0={with_h0} "
-             f"softplus={softplus}")
+    announce(f"waves per chain {dtype} out={out_dtype} gated={gated} h0={with_h0} softplus={softplus}")
     t = to_device(inp)
-    kw = dict(D=t["Dskip"], dt_bias=t.get("dt_bias"), z=t.get("z"), h0=t.get("h0"), delta_softplus=softplus,
-              out_dtype=out_dtype)
-    y1, h1 = mb.scan_fwd(t["u"], t["delta"], t["A"], t["B"], t["C"], return_last_state=True, **kw)
-    y2, h2, _ = mb.scan_fwd(t["u"], t["delta"], t["A"], t["B"], t["C"], return_last_state=True,
-                            return_ckpt=True, **kw)
-    torch.cuda.synchronize()
-    assert torch.equal(y1, y2), "y differs between the time-split and the plain kernel"
-    assert torch.equal(h1, h2), "h_last differs between the time-split and the plain kernel"
+    many = lambda x, n: None if x is None else x.expand(n, *x.shape[1:]).contiguous()
     tol = TOL_Y_BF16_OUT if out_dtype == torch.bfloat16 else 2e-3
-    check_against_oracle(inp, y1, h1, tol_y=tol, delta_softplus=softplus)
+    first = None
+    for n in copies:
+        args = [t[k] if k == "A" else many(t[k], n) for k in ("u", "delta", "A", "B", "C")]
+        kw = dict(D=t["Dskip"], dt_bias=t.get("dt_bias"), z=many(t.get("z"), n), h0=many(t.get("h0"), n),
+                  delta_softplus=softplus, out_dtype=out_dtype, return_last_state=True)
+        y, h = mb.scan_fwd(*args, **kw)
+        y_ck, h_ck, _ = mb.scan_fwd(*args, return_ckpt=True, **kw)
+        torch.cuda.synchronize()
+        assert torch.equal(y, y_ck) and torch.equal(h, h_ck), "storing checkpoints changed the results"
+        if first is None:
+            first = (y, h)
+            check_against_oracle(inp, y, h, tol_y=tol, delta_softplus=softplus)
+        assert torch.equal(y, first[0].expand_as(y)) and torch.equal(h, first[1].expand_as(h)), f"batch {n}"
 
 
 def test_resume_split_on_gpu():
@@ -244,28 +245,30 @@ def test_deterministic():
     assert torch.equal(y1, y2) and torch.equal(h1, h2)
 
 
-# (1, 5996, 1296): 750 eight-channel waves (4 dead lanes), 5 segments of 288 bytes
-# (the last 144), and the pre-pass in one piece per segment (3,000 waves: 6 per
-# SIMD either way); the other shapes take two pieces per segment.
-@pytest.mark.parametrize("shape", [(1, 64, 4096), (1, 61, 4112), (2, 24, 8192), (1, 8, 640), (1, 5996, 1296)])
+# Segments of 256 timesteps and of 512, the last one shorter, dead lanes; the pre-pass in one
+# piece per segment and in two (the last two); few chains and just over one per compute unit
+# (the last).
+@pytest.mark.parametrize("shape", [(1, 64, 4096), (1, 61, 4112), (2, 24, 8192), (1, 8, 2080), (1, 509, 16400),
+                                   (1, 2108, 8208)])
 @pytest.mark.parametrize("gated", [True, False])
 def test_time_segments(shape, gated):
-    """Few (batch, channel) rows and a long sequence: the tiled path cuts time into
-    segments, a pre-pass computes each segment's aggregate (in one or two pieces per
-    segment) and the scan folds them."""
+    """Few (batch, channel) rows and a long sequence: time is cut into segments, a pre-pass
+    computes each segment's aggregate (in one or two pieces per segment) and the scan folds
+    them."""
     nb, dim, L = shape
+    p = plan(shape)
+    assert p.nseg > 1 and p.pieces == (2 if dim > 500 else 1), p
     inp = make_inputs(nb, dim, L, 16, dtype="bf16", seed=15, with_h0=True, gated=gated, A_kind="random")
     announce(f"time segments {shape} gated={gated}")
     run_case(inp)
 
 
-def test_time_segments_f32_two_rounds():
-    """fp32 inputs at the 1.6B layer's width, (1, 4608, 2048): 7 segments of 320 bytes
-    (the last 128), the pre-pass in 2 pieces of 160 per segment.  Its 6,912 waves are
-    more than the 5 per SIMD that fit with fp32 inputs (83 VGPRs), so it runs in two
-    rounds."""
-    inp = make_inputs(1, 4608, 2048, 16, dtype="f32", seed=17, with_h0=True, A_kind="random")
-    announce("time segments fp32 (1, 4608, 2048), pre-pass in two rounds")
+@pytest.mark.parametrize("shape,segments", [((1, 512, 4096), 16), ((1, 4608, 2048), 1)])
+def test_time_segments_f32(shape, segments):
+    """fp32 inputs: 16 segments of 256 bytes, and the 1.6B layer's width, which is not cut."""
+    assert plan(shape).nseg == segments
+    inp = make_inputs(*shape, 16, dtype="f32", seed=17, with_h0=True, A_kind="random")
+    announce(f"time segments fp32 {shape}")
     run_case(inp)
 
 

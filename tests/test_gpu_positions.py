@@ -77,9 +77,9 @@ def check_states(inp, pos, h_at, h_last, rows=None):
     return worst
 
 
-# (batch, dim, L): tiled with a half chunk and dead lanes; row-per-thread
-# (L % 16 != 0); time-segmented shapes (few rows), where positions fall in
-# later segments; a short verify-like length.
+# (batch, dim, L): whole slices; 8 timesteps after them and dead lanes; time-segmented shapes
+# (few rows and from 2048 timesteps), where positions fall in later segments; one chain, not
+# cut; the verify length.
 @pytest.mark.parametrize("shape", [(2, 200, 1008), (2, 130, 1000), (1, 64, 4096), (1, 8, 640),
                                    (3, 72, 4112), (4, 96, 16)])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])

@@ -6,10 +6,9 @@ The cases are drawn once from a fixed seed, so the list and each case's inputs
 are the same on every run.  They cover:
 - batch 1-4 and dim 1-300 (dead lanes in the last 8-channel group whenever
   dim % 8 != 0);
-- forward lengths 0-2100: multiples of 16 take the tiled kernel (ending in a half
-  chunk when L % 32 == 16, cut into time segments when rows are few and
-  L >= 512), the others the row-per-thread kernel; dstate 16, and 1, 2, 4 or 8
-  on the row-per-thread kernel;
+- forward lengths 0-2100, multiples of 16 and others; dstate 16, and 1, 2, 4 or 8 on the
+  row-per-thread kernel;
+- forward lengths 2048-6000 of few rows, which are cut into time segments;
 - backward lengths that are multiples of 16 up to 1600, dstate 16;
 - fp32 or bf16 activations, fp32 or bf16 outputs;
 - each optional input (z, h0, Dskip, dt_bias, dh_last) present or absent;
@@ -22,6 +21,7 @@ import torch
 
 from gpu_util import announce, check_against_oracle, gpu_fwd, has_gpu
 from parity import TOL_Y, TOL_Y_BF16_OUT
+from plan_util import plan
 from paper_2401_13660_amd.inputs import bf16_bits_to_f32, f32_to_bf16_bits, make_inputs
 
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not has_gpu(), reason="needs a GPU")]
@@ -69,7 +69,18 @@ def _inputs(c: dict, seed: int):
     return inp
 
 
+def _segment_cases(seed: int, n: int):
+    rng = np.random.default_rng(seed)
+    cases = [_draw(rng, False) for _ in range(n)]
+    for c in cases:
+        c.update(N=16, batch=int(rng.integers(1, 3)), dim=int(rng.integers(1, 200)), L=int(rng.integers(2048, 6001)))
+        if rng.random() < 0.4:
+            c["L"] -= c["L"] % 16
+    return cases
+
+
 FWD_CASES = _cases(2401, 32, backward=False)
+SEG_CASES = _segment_cases(1366, 10)
 BWD_CASES = _cases(13660, 16, backward=True)
 
 
@@ -78,6 +89,18 @@ def test_random_forward(i):
     c = FWD_CASES[i]
     inp = _inputs(c, seed=100 + i)
     announce(f"random forward {i}: {_case_id(c)}")
+    out = torch.bfloat16 if c["out_bf16"] else torch.float32
+    y, h = gpu_fwd(inp, out_dtype=out, delta_softplus=c["softplus"])
+    check_against_oracle(inp, y, h, tol_y=TOL_Y_BF16_OUT if c["out_bf16"] else TOL_Y,
+                         delta_softplus=c["softplus"])
+
+
+@pytest.mark.parametrize("i", range(len(SEG_CASES)), ids=[_case_id(c) for c in SEG_CASES])
+def test_random_segmented_forward(i):
+    c = SEG_CASES[i]
+    assert plan((c["batch"], c["dim"], c["L"]), aligned=c["L"] % 16 == 0).nseg > 1
+    inp = _inputs(c, seed=400 + i)
+    announce(f"random segmented forward {i}: {_case_id(c)}")
     out = torch.bfloat16 if c["out_bf16"] else torch.float32
     y, h = gpu_fwd(inp, out_dtype=out, delta_softplus=c["softplus"])
     check_against_oracle(inp, y, h, tol_y=TOL_Y_BF16_OUT if c["out_bf16"] else TOL_Y,

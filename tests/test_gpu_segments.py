@@ -1,6 +1,6 @@
 """GPU parity of the time-segmented forward against the fp64 oracle, across decay rates.
 
-Shapes with few (batch, channel) rows cut the sequence into time segments: a pass
+Shapes with few (batch, channel) rows, which every test here asserts of its own, cut the sequence into time segments: a pass
 computes each segment's aggregate (P, H) -- the product of abar over the segment
 and the state reached from zero -- and the scan of segment s starts from h0 folded
 with the aggregates of segments 0..s-1.  How much the fold carries depends on the
@@ -16,9 +16,16 @@ import pytest
 import torch
 
 from gpu_util import announce, check_against_oracle, gpu_fwd, has_gpu
+from plan_util import plan
 from paper_2401_13660_amd.inputs import make_inputs
 
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not has_gpu(), reason="needs a GPU")]
+
+
+def _cut(shape, pieces=None):
+    """The library cuts this shape into time segments (with so many pre-pass pieces each)."""
+    p = plan(shape)
+    assert p.nseg > 1 and pieces in (None, p.pieces), p
 
 
 def _scaled_A(inp, per_channel):
@@ -31,6 +38,7 @@ def _scaled_A(inp, per_channel):
 @pytest.mark.parametrize("with_h0", [False, True])
 def test_fast_decay_stops_at_once(with_h0):
     # A = -500 (n + 1): abar underflows within a few timesteps
+    _cut((1, 256, 16384), pieces=1)
     inp = _scaled_A(make_inputs(1, 256, 16384, 16, seed=41, with_h0=with_h0), [500.0] * 256)
     announce(f"segments, fast decay (1, 256, 16384), h0={with_h0}")
     y, h = gpu_fwd(inp)
@@ -38,11 +46,13 @@ def test_fast_decay_stops_at_once(with_h0):
 
 
 def test_layer_decay_long_segments():
-    # (1, 2048, 32768): 256 waves, 16 segments of 2048 bytes, the layers' A = -(n + 1)
-    inp = make_inputs(1, 2048, 32768, 16, seed=42, with_h0=True)
-    announce("segments, layer decay (1, 2048, 32768)")
+    # (1, 1528, 20480): 191 chains, 5 segments of 4096 bytes in 4 pre-pass pieces each, the
+    # layers' A = -(n + 1)
+    _cut((1, 1528, 20480), pieces=4)
+    inp = make_inputs(1, 1528, 20480, 16, seed=42, with_h0=True)
+    announce("segments, layer decay (1, 1528, 20480)")
     y, h = gpu_fwd(inp)
-    rows = np.arange(0, 2048, 7)
+    rows = np.arange(0, 1528, 5)
     check_against_oracle(inp, y, h, rows=rows)
 
 
@@ -51,6 +61,7 @@ def test_slow_decay_reads_whole_segments(shape):
     # A = -1e-3 (n + 1): the product over a segment stays near 1, the carry of
     # every earlier segment reaches the end of the sequence
     nb, dim, L = shape
+    _cut(shape)
     inp = _scaled_A(make_inputs(nb, dim, L, 16, seed=43, with_h0=True), [1e-3] * dim)
     announce(f"segments, slow decay {shape}")
     y, h = gpu_fwd(inp)
@@ -63,6 +74,7 @@ def test_waves_mixing_fast_and_slow_decay():
     dim = 80
     scale = [500.0 if (d // 4) % 2 == 0 else 1e-2 for d in range(dim)]
     scale[-16:] = [500.0] * 16
+    _cut((2, dim, 8192))
     inp = _scaled_A(make_inputs(2, dim, 8192, 16, seed=44, with_h0=True), scale)
     announce("segments, mixed decay (2, 80, 8192)")
     y, h = gpu_fwd(inp)
@@ -74,6 +86,7 @@ def test_segmented_equals_itself_with_h_last_on_h0():
     # written over h0 the result must not change (bit for bit)
     import paper_2401_13660_amd as mb
     from gpu_util import to_device
+    _cut((1, 256, 16384))
     inp = make_inputs(1, 256, 16384, 16, seed=45, with_h0=True)
     announce("segments, h_last over h0 (1, 256, 16384)")
     y_ref, h_ref = gpu_fwd(inp)

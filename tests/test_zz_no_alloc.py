@@ -6,6 +6,7 @@ import pytest
 import torch
 
 from gpu_util import announce, check_against_oracle, has_gpu, to_device
+from plan_util import plan
 from paper_2401_13660_amd.inputs import make_inputs
 
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not has_gpu(), reason="needs a GPU")]
@@ -24,10 +25,13 @@ def _both(inp):
     return y_ref, h_ref, y, h
 
 
-# (1, 64, 4096): 16 time segments, (1, 40, 1024): 4 segments, (2, 72, 208): none
-# (a ragged tail chunk and dead lanes).  Each runs after the previous one.
-@pytest.mark.parametrize("shapes", [[(1, 64, 4096), (1, 40, 1024)], [(1, 61, 4112), (2, 72, 208)]])
+# Each pair: a carry, then a smaller one over what the first left in the array; ragged
+# lengths and dead lanes in the second pair, no segment at all in the third's last call.
+@pytest.mark.parametrize("shapes", [[(1, 64, 4096), (1, 40, 2048)], [(1, 61, 4112), (2, 21, 2083)],
+                                    [(1, 64, 4096), (2, 72, 208)]])
 def test_noalloc_equals_fwd_twice(shapes):
+    carry = [plan(s, aligned=s[2] % 16 == 0).carry for s in shapes]
+    assert carry[0] > carry[1] and (carry[1] > 0 or shapes[1][2] == 208)
     for i, (nb, dim, L) in enumerate(shapes):
         inp = make_inputs(nb, dim, L, 16, dtype="bf16", seed=40 + i, with_h0=True)
         announce(f"mb_scan_fwd_noalloc call {i + 1}: {(nb, dim, L)}")
@@ -51,13 +55,25 @@ def test_noalloc_h_last_on_h0():
 
 
 def test_noalloc_at_the_largest_carry():
-    """The 1.6B layer, (1, 4608, 65536): 7 segments whose pre-pass runs in 2 pieces
-    each, so the carry fills 13 planes of 4608 x 128 bytes (7.3 MiB of the 8 MiB
-    array).  Every output bit equals mb_scan_fwd's, whose rows are held to the fp64
-    oracle at this size by the full-size tests."""
+    """(1, 2304, 8192): 8 segments whose pre-pass runs in 2 pieces each, so the carry fills 15
+    planes of 2304 x 128 bytes, 4.2 MiB of the 8 MiB array.  Every output bit equals
+    mb_scan_fwd's, and sampled rows are held to the fp64 oracle."""
+    shape = (1, 2304, 8192)
+    assert plan(shape).carry == 15 * 2304 * 128
+    inp = make_inputs(*shape, 16, dtype="bf16", seed=44, with_h0=True)
+    announce(f"mb_scan_fwd_noalloc at {shape}, 4.2 MiB of carry")
+    y_ref, h_ref, y, h = _both(inp)
+    assert torch.equal(y, y_ref), f"y differs from mb_scan_fwd at {shape}"
+    assert torch.equal(h, h_ref), f"h_last differs from mb_scan_fwd at {shape}"
+    check_against_oracle(inp, y, h, rows=np.array([0, 1, 7, 8, 1151, 2295, 2303]))
+
+
+def test_noalloc_without_a_carry():
+    """The 1.6B layer, (1, 4608, 65536), is not cut: every bit equals mb_scan_fwd's."""
     from paper_2401_13660_amd.inputs import workload
     inp = workload("mambabyte1p6b_L65536")
-    announce("mb_scan_fwd_noalloc at (1, 4608, 65536), 7.3 MiB of carry")
+    assert plan((1, 4608, 65536)).carry == 0
+    announce("mb_scan_fwd_noalloc at (1, 4608, 65536), no carry")
     y_ref, h_ref, y, h = _both(inp)
     assert torch.equal(y, y_ref), "y differs from mb_scan_fwd at (1, 4608, 65536)"
     assert torch.equal(h, h_ref), "h_last differs from mb_scan_fwd at (1, 4608, 65536)"
