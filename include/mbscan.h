@@ -119,7 +119,7 @@ int mb_scan_fwd(const mb_scan_desc *desc,
  * and one for h0.  This entry point keeps that carry in a static device array of
  * 8 MiB instead: each GPU the library runs on holds its own copy until the
  * process ends.  A problem whose carry would exceed it returns MB_ERR_SHAPE
- * (on a 256-CU MI355X no carry passes 4.5 MiB).  The array keeps the last
+ * (on a 256-CU MI355X none does).  The array keeps the last
  * call's contents; nothing in it needs to start at zero (the segment pre-pass
  * writes every carry entry before the scan reads it).  Every call on one GPU
  * shares that GPU's array, so calls that may overlap in time on one GPU (other

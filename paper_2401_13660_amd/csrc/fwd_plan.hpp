@@ -15,17 +15,20 @@ enum Kernel {
     kRow,                             // one thread per row (scan_rowwise.hpp)
     kShort,                           // a sequence of 16 timesteps (scan_tiled.hpp)
     kRing,                            // slices dealt round the waves of a workgroup (scan_ring.hpp)
+    kChunk,                           // one wave per chain, chunks of 32 timesteps (scan_chunk.hpp)
 };
 
 struct Shape {
     int64_t batch, dim, L, dstate;
+    int in_bytes, out_bytes;          // per activation
+    bool gate;
     bool aligned16;                   // every activation and y on a 16-byte boundary
     bool ckpt;                        // checkpoints are stored
 };
 
 struct Fwd {
     Kernel kernel;
-    int64_t chains;                   // of all time segments (kRing)
+    int64_t chains;                   // of all time segments (kRing, kChunk)
     int64_t nseg, seg_len, pieces;    // time segments (1: none), their length, pre-pass pieces per segment
     uint32_t log_w;                   // waves per chain: 1 << log_w
     int64_t workgroups;
@@ -82,7 +85,8 @@ inline uint32_t waves_per_chain_log2(int64_t chains, int64_t slices, int64_t cus
 //   and 26; (1, 64, 2048) 30 and 23, (1, 64, 1536) 23 either way); up to 5/8 from 3072 ((1,
 //   1280, 3056), 160 chains, 43 and 40, (1, 1280, 2048) 30 either way); below 3/4 from 4096
 //   ((1, 1528, 6000), 191 chains, 80 and 75, (1, 1528, 3056) 43 and 45); below 7/8 from 16384
-//   ((1, 1536, 16384), 192 chains, 207 and 164, (1, 1792, 16384), 224 chains, 208 and 210).
+//   ((1, 1536, 16384), 192 chains, 207 and 164, (1, 1792, 16384), 224 chains, 208 and 210), and
+//   from 4/5 into 8 for evenness ((1, 1664, 16384), 208 chains, 209 in 4 and 191).
 // - just over one chain per CU, where a few CUs take two and set the time, from 8192
 //   timesteps into 8: (1, 2112, 8192), 264 chains, 146 and 129, (1, 2304, 32768), 288 chains,
 //   571 and 492; (1, 2432, 16384), 304 chains, 287 and 307.
@@ -99,6 +103,7 @@ inline int64_t segments(int64_t chains, int64_t L, int64_t cus, int64_t *seg_len
     const int64_t least_L = chains * 8 <= cus * 4 ? 2048 : chains * 8 <= cus * 5 ? 3072
                             : chains * 8 < cus * 6 ? 4096 : 16384;
     if (chains * 8 < cus * 7 && L >= least_L) n = 4 * cus / chains;
+    if (chains * 5 >= cus * 4 && n > 1) n = 8;
     if (chains > cus && chains * 8 <= cus * 9 && L >= 8192) n = 8;
     if (n > L / 256) n = L / 256;
     if (n > 128) n = 128;
@@ -112,6 +117,45 @@ inline int64_t segments(int64_t chains, int64_t L, int64_t cus, int64_t *seg_len
     *seg_len = len;
     *pieces = m;
     return (L + len - 1) / len;
+}
+
+// Time segments of the chunk kernel: with fewer than 3/8 of the waves that fill the chip at 2
+// per SIMD, the most that make at most twice as many, of at least 256 timesteps; the pre-pass
+// in 2 pieces per segment where that shortens the busiest SIMD's work, ceil(2 w / simds) / 2
+// below ceil(w / simds) for the w waves of whole segments.
+inline int64_t chunk_segments(int64_t chains, int64_t L, int64_t cus, int64_t *seg_len, int64_t *pieces) {
+    const int64_t resident = 8 * cus, simds = 4 * cus;
+    int64_t n = chains * 8 < resident * 3 ? 2 * resident / chains : 1, m = 1;
+    if (n > L / 256) n = L / 256;
+    *seg_len = L;
+    *pieces = 1;
+    if (n <= 1) return 1;
+    const int64_t w = chains * (n - 1);
+    if ((2 * w + simds - 1) / simds < 2 * ((w + simds - 1) / simds)) m = 2;
+    const int64_t unit = 32 * m, len = ((L + n - 1) / n + unit - 1) / unit * unit;
+    *seg_len = len;
+    *pieces = m;
+    return (L + len - 1) / len;
+}
+
+// The chunk kernel takes whole slices in aligned rows where the problem moves more bytes than
+// the 256 MB of the Infinity Cache hold and it is the faster one.  In us, ring and chunk:
+// - fp32 in, from 7 chains per CU, (4, 3584, 2048) 153 and 145, (16, 3584, 1024) 318 and 263
+//   ((4, 3072, 2048), 6 per CU, 132 and 140; (16, 3584, 256), 235 MB, 70 and 67); with
+//   checkpoints from 6, (4, 3072, 2048) 154 and 146, (2, 4608, 2048), 4.5 per CU, 127 and 142;
+// - fp32 in, few chains, which both cut into segments: from 1/4 to 7/8 of a chain per CU, (1,
+//   1280, 65536) 700 and 631, (1, 512, 65536) 293 and 286, (1, 256, 65536) 160 and 176, (1,
+//   1792, 65536) 819 and 883; and up to 1.2, (1, 2112, 16384) 307 and 268, (1, 2688, 16384)
+//   315 and 326;
+// - bf16 in, with checkpoints, from 16 chains per CU: (16, 3584, 512) 150 and 138, (64, 3584,
+//   256) 327 and 299, (8, 3584, 2048) 290 either way.
+inline bool chunk_is_faster(const Shape &s, int64_t chains, int64_t cus) {
+    if (!s.aligned16 || s.L % kSlice != 0) return false;
+    const int64_t per_step = s.in_bytes * (s.gate ? 3 : 2) + s.out_bytes + (s.ckpt ? 4 : 0);
+    if (s.batch * s.dim <= (int64_t(256) << 20) / (s.L * per_step)) return false;
+    if (s.in_bytes == 2) return s.ckpt && chains > 16 * cus;
+    if (chains > cus) return chains * 5 <= cus * 6 || chains >= (s.ckpt ? 6 : 7) * cus;
+    return chains * 4 >= cus && chains * 8 < cus * 7;
 }
 
 // The plan of a scan with at least one row and one timestep; cus_of says how many compute
@@ -133,6 +177,14 @@ inline Fwd fwd(const Shape &s, int64_t (*cus_of)()) {
         return f;
     }
     const int64_t cus = cus_of();
+    if (chunk_is_faster(s, base, cus)) {
+        f.kernel = kChunk;
+        f.nseg = chunk_segments(base, s.L, cus, &f.seg_len, &f.pieces);
+        f.chains = base * f.nseg;
+        f.workgroups = (f.chains + 3) / 4;
+        f.threads = 256;
+        return f;
+    }
     f.kernel = kRing;
     f.nseg = segments(base, s.L, cus, &f.seg_len, &f.pieces);
     f.chains = base * f.nseg;

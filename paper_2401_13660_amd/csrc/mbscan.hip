@@ -12,6 +12,7 @@
 #include "fwd_plan.hpp"
 #include "mbscan.h"
 #include "scan_bwd.hpp"
+#include "scan_chunk.hpp"
 #include "scan_params.hpp"
 #include "scan_ring.hpp"
 #include "scan_rowwise.hpp"
@@ -64,14 +65,50 @@ hipError_t fwd_rowwise(ScanParams &p, void *stream) {
                   stream);
 }
 
+// The ring or the chunk kernel, after the pre-pass where the sequence is cut into segments;
+// their carry in `lent` or, if that is null, in memory allocated on the stream.
+template <int IN, int OUT, bool GATE, bool SP>
+hipError_t fwd_chains_sp(ScanParams &p, const mbs::plan::Fwd &f, void *stream, float *lent) {
+    namespace T = mbs::tiled;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    float *carry = lent;
+    hipError_t e = hipSuccess;
+    if (f.nseg > 1) {
+        if (!lent) {
+            e = hipMallocAsync(reinterpret_cast<void **>(&carry), mbs::plan::carry_bytes(p.batch * p.dim, f), st);
+            if (e != hipSuccess) return e;
+        }
+        int64_t piece_len = f.seg_len / f.pieces, npieces = f.pieces * (f.nseg - 1);
+        const int64_t waves = f.chains / f.nseg * npieces;
+        const int64_t blocks = (waves + T::kWavesPerGroup - 1) / T::kWavesPerGroup;
+        void *args[] = {&p, &piece_len, &npieces, &carry};
+        e = hipLaunchKernel(reinterpret_cast<const void *>(&T::scan_seg_agg<IN, SP>), dim3((unsigned)blocks),
+                            dim3(T::kThreads), args, sizeof(T::WaveSmemPre) * T::kWavesPerGroup, st);
+    }
+    if (e == hipSuccess)
+        e = f.kernel == mbs::plan::kChunk ? mbs::chunk::fwd_chunk<IN, OUT, GATE, SP>(p, f, st, carry)
+                                          : mbs::ring::fwd_ring<IN, OUT, GATE, SP>(p, f, st, carry);
+    if (carry && !lent) {
+        const hipError_t fr = hipFreeAsync(carry, st);
+        if (e == hipSuccess) e = fr;
+    }
+    return e;
+}
+
+template <int IN, int OUT, bool GATE>
+hipError_t fwd_chains(ScanParams &p, const mbs::plan::Fwd &f, void *stream, float *lent) {
+    return p.delta_softplus ? fwd_chains_sp<IN, OUT, GATE, true>(p, f, stream, lent)
+                            : fwd_chains_sp<IN, OUT, GATE, false>(p, f, stream, lent);
+}
+
 template <int IN, int OUT>
 hipError_t fwd_dispatch_n(ScanParams &p, const mbs::plan::Fwd &f, int64_t N, void *stream, float *lent) {
     switch (f.kernel) {
         case mbs::plan::kShort:
             return p.z ? mbs::tiled::fwd_short<IN, OUT, true>(p, stream) : mbs::tiled::fwd_short<IN, OUT, false>(p, stream);
         case mbs::plan::kRing:
-            return p.z ? mbs::ring::fwd_ring<IN, OUT, true>(p, f, stream, lent)
-                       : mbs::ring::fwd_ring<IN, OUT, false>(p, f, stream, lent);
+        case mbs::plan::kChunk:
+            return p.z ? fwd_chains<IN, OUT, true>(p, f, stream, lent) : fwd_chains<IN, OUT, false>(p, f, stream, lent);
         default: break;
     }
     switch (N) {
@@ -397,8 +434,7 @@ int scan_fwd_impl(const mb_scan_desc *desc, const void *u, const void *delta, co
     p.delta_softplus = desc->delta_softplus ? 1 : 0;
 
     if (ck) {
-        // checkpoints exist on the tiled path only: dstate 16, L a multiple of 16,
-        // 16-byte aligned activations and y
+        // checkpoints: dstate 16, L a multiple of 16, 16-byte aligned activations and y
         if (N != 16 || L % 16 != 0 || L >= (int64_t(1) << 25)) return MB_ERR_UNSUPPORTED;
         const void *a16[] = {u, delta, z, Bmat, Cmat, y};
         for (const void *q : a16)
@@ -416,13 +452,14 @@ int scan_fwd_impl(const mb_scan_desc *desc, const void *u, const void *delta, co
         bool aligned16 = true;
         for (const void *q : {u, delta, z, Bmat, Cmat, static_cast<const void *>(y)})
             if (q && !aligned(q, 16)) aligned16 = false;
-        f = mbs::plan::fwd({B, D, L, N, aligned16, ck != nullptr}, &mbs::tiled::device_cus);
-        if (ck && f.kernel != mbs::plan::kRing) return MB_ERR_UNSUPPORTED;
+        f = mbs::plan::fwd({B, D, L, N, (int)in_sz, (int)out_sz, z != nullptr, aligned16, ck != nullptr},
+                           &mbs::tiled::device_cus);
+        if (ck && f.kernel == mbs::plan::kRow) return MB_ERR_UNSUPPORTED;
     }
 
-    if (npos > 0 && (L == 0 || f.kernel == mbs::plan::kRow)) {
-        // Position -1 and invalid positions, before h_last (which may be h0) is written; at
-        // dstate 16 the scan's kernels fill these slots themselves.
+    if (npos > 0 && (L == 0 || f.kernel == mbs::plan::kRow || f.kernel == mbs::plan::kChunk)) {
+        // Position -1 and invalid positions, before h_last (which may be h0) is written; the
+        // ring and the 16-timestep kernel fill these slots themselves.
         const dim3 block(256), grid((unsigned)((hpos_elems + 255) / 256));
         int64_t n_arg = N;
         void *args[] = {&p, &n_arg};

@@ -499,30 +499,9 @@ __global__ __launch_bounds__(kMaxWaves * 64) void scan_fwd_ring(ScanParams p, Ri
 // ---- host side ------------------------------------------------------------------
 
 template <int IN, int OUT, bool GATE, bool SP>
-hipError_t fwd_ring_sp(ScanParams &p, const plan::Fwd &f, void *stream, float *lent) {
-    hipStream_t st = static_cast<hipStream_t>(stream);
+hipError_t fwd_ring(ScanParams &p, const plan::Fwd &f, hipStream_t st, const float *carry) {
     RingParams g{};
     g.n_cg = (uint32_t)((p.dim + kCh - 1) / kCh);
-    float *carry = nullptr;
-    hipError_t e;
-    if (f.nseg > 1) {
-        if (lent) {
-            carry = lent;
-        } else {
-            e = hipMallocAsync(reinterpret_cast<void **>(&carry), plan::carry_bytes(p.batch * p.dim, f), st);
-            if (e != hipSuccess) return e;
-        }
-        int64_t piece_len = f.seg_len / f.pieces, npieces = f.pieces * (f.nseg - 1);
-        const int64_t waves = (int64_t)g.n_cg * p.batch * npieces;
-        const int64_t blocks = (waves + tiled::kWavesPerGroup - 1) / tiled::kWavesPerGroup;
-        void *args[] = {&p, &piece_len, &npieces, &carry};
-        e = hipLaunchKernel(reinterpret_cast<const void *>(&tiled::scan_seg_agg<IN, SP>), dim3((unsigned)blocks),
-                            dim3(tiled::kThreads), args, sizeof(tiled::WaveSmemPre) * tiled::kWavesPerGroup, st);
-        if (e != hipSuccess) {
-            if (!lent) (void)hipFreeAsync(carry, st);
-            return e;
-        }
-    }
     g.nseg = (uint32_t)f.nseg;
     g.seg_len = (uint32_t)f.seg_len;
     g.pieces = (uint32_t)f.pieces;
@@ -533,19 +512,8 @@ hipError_t fwd_ring_sp(ScanParams &p, const plan::Fwd &f, void *stream, float *l
     const void *fn = p.npos > 0 ? reinterpret_cast<const void *>(&scan_fwd_ring<IN, OUT, GATE, SP, kPositions>)
                      : p.ck     ? reinterpret_cast<const void *>(&scan_fwd_ring<IN, OUT, GATE, SP, kCheckpoints>)
                                 : reinterpret_cast<const void *>(&scan_fwd_ring<IN, OUT, GATE, SP, kPlain>);
-    e = hipLaunchKernel(fn, dim3((unsigned)f.workgroups), dim3(f.threads), args,
-                        sizeof(WaveSmem) * (f.threads / 64) + 4 * kMaxWaves, st);
-    if (carry && !lent) {
-        const hipError_t fr = hipFreeAsync(carry, st);
-        if (e == hipSuccess) e = fr;
-    }
-    return e;
-}
-
-template <int IN, int OUT, bool GATE>
-hipError_t fwd_ring(ScanParams &p, const plan::Fwd &f, void *stream, float *lent) {
-    return p.delta_softplus ? fwd_ring_sp<IN, OUT, GATE, true>(p, f, stream, lent)
-                            : fwd_ring_sp<IN, OUT, GATE, false>(p, f, stream, lent);
+    return hipLaunchKernel(fn, dim3((unsigned)f.workgroups), dim3(f.threads), args,
+                           sizeof(WaveSmem) * (f.threads / 64) + 4 * kMaxWaves, st);
 }
 
 }  // namespace ring

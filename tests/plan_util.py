@@ -11,7 +11,7 @@ CXX = os.environ.get("CXX", "g++")
 
 
 class Plan(NamedTuple):
-    kernel: str          # row, short or ring
+    kernel: str          # row, short, ring or chunk
     nseg: int            # time segments (1: none)
     seg_len: int
     pieces: int          # pre-pass pieces per segment
@@ -34,8 +34,9 @@ def _exe() -> str:
     return exe
 
 
-def plans(shapes, *, dstate=16, aligned=True, ckpt=False, cus=256):
-    lines = "".join(f"{b} {d} {L} {dstate} {int(aligned)} {int(ckpt)} {cus}\n" for b, d, L in shapes)
+def plans(shapes, *, dstate=16, dtype="bf16", out_bytes=4, gate=True, aligned=True, ckpt=False, cus=256):
+    lines = "".join(f"{b} {d} {L} {dstate} {2 if dtype == 'bf16' else 4} {out_bytes} {int(gate)} {int(aligned)} "
+                    f"{int(ckpt)} {cus}\n" for b, d, L in shapes)
     out = subprocess.run([_exe()], input=lines, check=True, capture_output=True, text=True).stdout
     return [Plan(w[0], *map(int, w[1:])) for w in (line.split() for line in out.splitlines())]
 

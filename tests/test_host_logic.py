@@ -33,7 +33,7 @@ def _rule(chains: int, L: int):
     """segments, their length, pre-pass pieces."""
     n = 1
     if chains < 224 and L >= (2048 if chains <= 128 else 3072 if chains <= 160 else 4096 if chains < 192 else 16384):
-        n = 1024 // chains
+        n = 1024 // chains if chains < 205 else 8
     if 256 < chains <= 288 and L >= 8192:
         n = 8
     n = min(n, L // 256, 128)
@@ -48,7 +48,7 @@ def _rule(chains: int, L: int):
 
 
 def test_segments_follow_the_rule():
-    shapes = [(1, 8 * c, L) for c in (1, 3, 8, 31, 100, 128, 129, 160, 161, 191, 192, 223, 224, 255, 256, 257, 264, 288, 289, 448,
+    shapes = [(1, 8 * c, L) for c in (1, 3, 8, 31, 100, 128, 129, 160, 161, 191, 192, 204, 205, 223, 224, 255, 256, 257, 264, 288, 289, 448,
                                       576, 1792)
               for L in (16, 256, 1008, 2047, 2048, 3071, 4095, 4096, 8190, 8192, 20480, 65536, 2 ** 24)]
     for (nb, dim, L), p in zip(shapes, plans(shapes, aligned=False)):
@@ -67,9 +67,36 @@ def test_segments_follow_the_rule():
 
 
 def test_every_carry_fits_the_allocation_free_array():
-    """On 256 compute units no carry passes 4.5 MiB of the allocation-free call's 8 MiB."""
+    """On 256 compute units no carry exceeds the allocation-free call's 8 MiB."""
     shapes = [(1, 8 * c, L) for c in range(1, 400) for L in (2048, 4096, 8192, 16384, 20480, 32768, 65536, 2 ** 24)]
-    assert 4 << 20 < max(p.carry for p in plans(shapes)) <= 4.5 * 2 ** 20
+    for dtype in ("bf16", "f32"):
+        assert 4 << 20 < max(p.carry for p in plans(shapes, dtype=dtype)) <= 8 << 20
+
+
+def test_chunk_kernel_where_it_is_faster():
+    """fp32 and, with checkpoints, bf16 problems of more than 256 MB whose chains are many, or few
+    enough to be cut; whole slices in aligned rows only."""
+    mb256 = 256 << 20
+
+    def kernel(chains, nbytes, **kw):                    # the length that just passes, or not
+        kw = {"dtype": "f32", **kw}
+        per = (8 if kw["dtype"] == "bf16" else 16) + (4 if kw.get("ckpt") else 0) + (2 if kw["dtype"] == "bf16" else 0)
+        L = (nbytes // (8 * chains * per * 16) + (nbytes > mb256)) * 16
+        return plan((1, 8 * chains, L), **kw).kernel
+
+    more, less = mb256 + 1, mb256
+    for chains, want in {63: "ring", 64: "chunk", 223: "chunk", 224: "ring", 256: "ring", 257: "chunk", 307: "chunk",
+                         308: "ring", 1791: "ring", 1792: "chunk", 28672: "chunk"}.items():
+        assert kernel(chains, more) == want, chains
+        assert kernel(chains, less) == "ring", chains
+        assert kernel(chains, more, aligned=False) == "ring"
+    assert [kernel(c, more, ckpt=True) for c in (1535, 1536)] == ["ring", "chunk"]
+    bf = dict(dtype="bf16")
+    assert plan((16, 3584, 512), **bf).kernel == "ring"
+    assert [plan(s, ckpt=True, **bf).kernel for s in ((16, 3584, 512), (16, 3584, 320), (8, 3584, 2048))] == ["chunk", "ring", "ring"]
+    assert plan((16, 3584, 1009), dtype="f32", aligned=True).kernel == "ring"
+    segmented = plan((1, 1280, 65536), dtype="f32")
+    assert segmented[:4] == ("chunk", 25, 2624, 1) and segmented.workgroups == 25 * 160 // 4
 
 
 def test_waves_per_chain():
