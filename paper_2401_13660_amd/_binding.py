@@ -11,12 +11,12 @@ from __future__ import annotations
 import contextlib
 import ctypes
 import os
+import warnings
 
 import torch
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libmbscan.so")
-FAST_PATH = os.path.join(_PKG, "_fastcall.so")
 
 MB_F32, MB_BF16 = 0, 1
 _STATUS_OK = 0
@@ -81,13 +81,21 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
 def _load_fast(lib):
     """The module built from csrc/fastcall.cpp, calling the functions of ``lib``.  It takes
     the calls whose tensors are plain, dense, of the expected shapes and on the current
-    device, does what the functions below do with them, and returns None for any other."""
-    if not os.path.exists(FAST_PATH):
-        raise MBScanError(f"{FAST_PATH} is not built; run `python -m paper_2401_13660_amd.build` "
-                          "(or __graft_entry__.build()) first")
+    device, does what the functions below do with them, and returns None for any other.
+    Where it is not built, or against another torch, the Python code takes every call."""
     if _raw_stream is None or _cur_device is None:
         return None
-    from . import _fastcall
+    try:
+        from . import _fastcall
+    except ImportError as e:
+        why = str(e)
+    else:
+        built_for = getattr(_fastcall, "torch_version", None)
+        why = None if built_for == torch.__version__ else f"built for torch {built_for}, not {torch.__version__}"
+    if why is not None:
+        warnings.warn(f"the native entry points of the binding are not used ({why}): calls are marshalled in Python. "
+                      "`python -m paper_2401_13660_amd.build` builds them.", RuntimeWarning, stacklevel=3)
+        return None
     at = [ctypes.cast(fn, _VP).value for fn in (lib.mb_scan_fwd, lib.mb_scan_fwd_states, lib.mb_scan_fwd_ckpt,
                                                 lib.mb_scan_step, lib.mb_conv1d_fwd, lib.mb_conv1d_step,
                                                 lib.mb_verify_rank)]

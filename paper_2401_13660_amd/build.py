@@ -57,7 +57,8 @@ def build_fastcall(verbose: bool = False) -> str:
     out = os.path.join(PKG, "_fastcall.so")
     tmp = out + ".tmp"
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unused-function",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", os.path.join(ROOT, "include"),
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DMB_TORCH_VERSION="{torch.__version__}"', "-I", os.path.join(ROOT, "include"),
            "-isystem", os.path.join(base, "include"),
            "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"),
            "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "fastcall.cpp"), "-o", tmp,

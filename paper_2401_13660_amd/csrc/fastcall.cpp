@@ -353,4 +353,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, methods, 
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__fastcall() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__fastcall() {
+    PyObject *m = PyModule_Create(&module);
+    // the torch whose object layouts this was compiled against: the binding uses no other
+    if (m && PyModule_AddStringConstant(m, "torch_version", MB_TORCH_VERSION) != 0) Py_CLEAR(m);
+    return m;
+}
