@@ -1,9 +1,10 @@
 """The binding's native entry points against its Python code.
 
-Well-formed calls go through _fastcall; the same call with it switched off runs the checks
-and allocations of the Python functions.  Both make one library call on the same inputs, so
-every result must be the same bits, with the same number of outputs, types and shapes; and
-what the native entry points do not take must end in the same errors.
+Well-formed calls go through _fastcall, which must take them; the same call with it switched
+off runs the checks and allocations of the Python functions.  Both make one library call on
+the same inputs, so every result must be the same bits, with the same number of outputs, types
+and shapes; and what the native entry points do not take, which they must decline, ends in the
+same errors.
 """
 import numpy as np
 import pytest
@@ -15,21 +16,46 @@ from paper_2401_13660_amd.inputs import make_conv_inputs, make_inputs
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not has_gpu(), reason="needs a GPU")]
 
 
+class _Watched:
+    """The native module, and for each call made to it whether it was taken."""
+
+    def __init__(self, fast):
+        self.fast, self.taken = fast, []
+
+    def __getattr__(self, name):
+        def entry(*args):
+            r = getattr(self.fast, name)(*args)
+            self.taken.append(r is not None)
+            return r
+        return entry
+
+
 @pytest.fixture
-def both(monkeypatch):
-    """both(call): its results through the native entry points and through Python."""
+def watched(monkeypatch):
     from paper_2401_13660_amd import _binding
     _binding.load_library()
     assert _binding._fast is not None
+    w = _Watched(_binding._fast)
+    monkeypatch.setattr(_binding, "_fast", w)
+    return w
 
-    def run(call):
+
+@pytest.fixture
+def both(watched, monkeypatch):
+    """both(call): its results through the native entry points, which take it (or decline it,
+    taken=False), and through Python."""
+    from paper_2401_13660_amd import _binding
+
+    def run(call, taken=True):
         out = []
         for native in (True, False):
             with monkeypatch.context() as m:
                 if not native:
                     m.setattr(_binding, "_fast", None)
+                watched.taken.clear()
                 r = call()
                 torch.cuda.synchronize()
+                assert watched.taken == ([taken] if native else []), watched.taken
             out.append(r if isinstance(r, tuple) else (r,))
         return out
     return run
@@ -120,12 +146,49 @@ def test_refusals_and_errors_are_the_same(both):
                 said.append(str(e))
             return torch.zeros(1)
 
-        both(call)
+        both(call, taken="out" in kw)                    # an output over an input: the library refuses it
         assert said[0] is not None and said[0] == said[1], said
     # a subclass is no plain tensor: the Python code takes it
-    _same(*both(lambda: mb.scan_fwd(**dict(a, u=t["u"].as_subclass(Tagged)))))
-    # outputs of a call under no stream but torch's current one
-    s = torch.cuda.Stream()
-    s.wait_stream(torch.cuda.current_stream())
-    with torch.cuda.stream(s):
-        _same(*both(lambda: mb.scan_fwd(**a)))
+    _same(*both(lambda: mb.scan_fwd(**dict(a, u=t["u"].as_subclass(Tagged))), taken=False))
+
+
+def test_calls_run_on_the_current_stream(watched):
+    """Each entry reads an input that work queued before it on a side stream still has to write:
+    launched on any other stream, it would find the old values."""
+    import paper_2401_13660_amd as mb
+    inp = make_inputs(1, 64, 32, 16, dtype="f32", seed=7, with_h0=True)
+    t = to_device(inp)
+    c = make_conv_inputs(1, 64, 32, 4, dtype="f32", seed=8, with_state=True)
+    x, w, bias, st = (dev_tensor(v) for v in (c.x, c.w, c.bias, c.state))
+    one = {k: t[k][..., 0].contiguous() for k in ("u", "delta", "B", "C")}
+    pos = torch.zeros((1, 1), dtype=torch.int32, device="cuda:0")
+    logits = torch.randn(1, 5, 256, device="cuda:0")
+    draft = logits.argsort(-1)[..., -2].to(torch.int32).contiguous()     # rank 2; of equal logits 1
+    scan = lambda v, **k: mb.scan_fwd(v, t["delta"], t["A"], t["B"], t["C"], **k)  # noqa: E731
+    calls = {
+        "scan_fwd": (t["u"], scan),
+        "scan_fwd, positions": (t["u"], lambda v: scan(v, positions=pos)[0]),
+        "scan_fwd, checkpoints": (t["u"], lambda v: scan(v, return_ckpt=True)[0]),
+        "scan_step": (one["u"], lambda v: mb.scan_step(t["h0"].clone(), v, one["delta"], t["A"], one["B"], one["C"])),
+        "conv1d": (x, lambda v: mb.conv1d(v, w, bias)),
+        "conv1d_step": (x[..., 0].contiguous(), lambda v: mb.conv1d_step(st.clone(), v, w, bias)),
+        "verify_rank": (logits, lambda v: mb.verify_rank(v, draft, 1)[0]),
+    }
+    busy, side = torch.randn(8192, 8192, device="cuda:0"), torch.cuda.Stream()
+    busy @ busy                                          # the library's kernels are loaded
+    for name, (new, call) in calls.items():
+        announce(f"fastcall, side stream: {name}")
+        want, old = call(new), call(torch.zeros_like(new))
+        assert not torch.equal(want, old)
+        v = torch.zeros_like(new)
+        torch.cuda.synchronize()
+        watched.taken.clear()
+        with torch.cuda.stream(side):
+            for _ in range(4):
+                busy @ busy                              # milliseconds, ahead of the write
+            v.copy_(new)
+            got = call(v)
+            queued = not side.query()                    # the call was made while the write was pending
+        torch.cuda.synchronize()
+        assert queued and watched.taken == [True], (name, queued, watched.taken)
+        assert torch.equal(got, want), name
