@@ -193,10 +193,11 @@ __global__ __launch_bounds__(kMaxWaves * 64) void scan_fwd_ring(ScanParams p, Ri
     // Loads never branch: past the last full slice a wave reads its first again (never
     // consumed).  A wave's next slice is asked for as soon as the last one's registers are
     // free, except where the 128 VGPRs do not hold it beside the exponentials (14 registers
-    // of fp32, or the state and positions to record): then after them, before the wait for
-    // the state.  Spilled instead, (4, 3584, 2048) fp32 took 242 us, this way 156; bf16 with
-    // checkpoints (4, 3584, 8192) 577 and 564.
-    constexpr bool kLateLoads = IN == 0 || REC != kPlain;
+    // of fp32, or what checkpoints with a gate, or positions, need): then after them, before the
+    // wait for the state.  Spilled instead, (4, 3584, 2048) fp32 took 242 us, this way 156; bf16
+    // with checkpoints (4, 3584, 8192) 577 and 564.  Without a gate checkpoints spill nothing, and
+    // (1, 3584, 46656) took 843 us with early loads and 916 with late ones.
+    constexpr bool kLateLoads = IN == 0 || REC == kPositions || (REC == kCheckpoints && GATE);
     const uint32_t oa = act_row + 2 * q, ob = bc_row + 2 * j;
     auto issue_loads = [&](uint32_t i) {
         const uint32_t t0 = t_begin + (i < nfull ? i : (uint32_t)r) * kS;
