@@ -24,6 +24,8 @@ struct Shape {
     bool gate;
     bool aligned16;                   // every activation and y on a 16-byte boundary
     bool ckpt;                        // checkpoints are stored
+    int64_t npos;                     // states recorded per batch element
+    bool h0;                          // a first state is given
 };
 
 struct Fwd {
@@ -158,6 +160,23 @@ inline bool chunk_is_faster(const Shape &s, int64_t chains, int64_t cus) {
     return chains * 4 >= cus && chains * 8 < cus * 7;
 }
 
+// The row kernel takes a few timesteps of many rows that start from zero: a wave of the ring
+// kernel is set up for 8 channels, one of the row kernel for 64 rows, but it reads first states
+// row by row.  In us, ring and row, with a gate, y in the inputs' type:
+// - bf16 in, up to 8 timesteps, from 16 chains per CU and 16 more per timestep: (16, 4608, 1), 36
+//   per CU, 8.0 and 7.4, with 2 8.7 and 8.9; (28, 4608, 2), 63, 13.1 and 11.7, with 3 13.8 and
+//   13.7; (64, 4608, 8), 144, 42 and 39; (200, 3584, 2), 350, 62 and 45;
+// - fp32 in, up to 4, from 8 and 24 more: (16, 4608, 1) 7.7 and 7.3, (28, 4608, 2) 12.5 and 11.7,
+//   with 3 13.4 and 14.2; (200, 3584, 3) 63 and 52, with 6 77 and 90;
+// - with a first state, bf16 (64, 4608, 2) 29.5 and 29.8, (200, 3584, 4) 75 either way.
+// Not where states are recorded: bf16 (31, 5112, 1) with 8 positions 26 and 60.  The row kernel
+// forms its sums in the order of the ring kernel's last timesteps, so that recording changes no
+// bit.
+inline bool row_is_faster(const Shape &s, int64_t chains, int64_t cus) {
+    if (s.h0 || s.npos > 0) return false;
+    return s.in_bytes == 2 ? s.L <= 8 && chains >= (16 + 16 * s.L) * cus : s.L <= 4 && chains >= (8 + 24 * s.L) * cus;
+}
+
 // The plan of a scan with at least one row and one timestep; cus_of says how many compute
 // units the device has, asked only where a rule needs it.
 inline Fwd fwd(const Shape &s, int64_t (*cus_of)()) {
@@ -177,6 +196,7 @@ inline Fwd fwd(const Shape &s, int64_t (*cus_of)()) {
         return f;
     }
     const int64_t cus = cus_of();
+    if (row_is_faster(s, base, cus)) return f;
     if (chunk_is_faster(s, base, cus)) {
         f.kernel = kChunk;
         f.nseg = chunk_segments(base, s.L, cus, &f.seg_len, &f.pieces);

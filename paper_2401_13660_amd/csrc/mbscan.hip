@@ -452,7 +452,8 @@ int scan_fwd_impl(const mb_scan_desc *desc, const void *u, const void *delta, co
         bool aligned16 = true;
         for (const void *q : {u, delta, z, Bmat, Cmat, static_cast<const void *>(y)})
             if (q && !aligned(q, 16)) aligned16 = false;
-        f = mbs::plan::fwd({B, D, L, N, (int)in_sz, (int)out_sz, z != nullptr, aligned16, ck != nullptr},
+        f = mbs::plan::fwd({B, D, L, N, (int)in_sz, (int)out_sz, z != nullptr, aligned16, ck != nullptr, npos,
+                            h0 != nullptr},
                            &mbs::tiled::device_cus);
         if (ck && f.kernel == mbs::plan::kRow) return MB_ERR_UNSUPPORTED;
     }

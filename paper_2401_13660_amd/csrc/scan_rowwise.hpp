@@ -2,7 +2,8 @@
 //
 // Each thread walks its row in time order, holding the N-state of eq. (2) in
 // registers.  It takes what the kernels of dstate 16 do not (dstate < 16, sequences of
-// 2^25 timesteps and more); it is correct for every legal argument combination.
+// 2^25 timesteps and more, 2^26 chains of 8 channels and more) and a few timesteps of many
+// rows (plan::row_is_faster); it is correct for every legal argument combination.
 #pragma once
 
 #include "device_math.hpp"
@@ -34,15 +35,23 @@ __global__ __launch_bounds__(64) void scan_fwd_rowwise(ScanParams p) {
         const float v = Act<IN>::ld(p.delta, base + t) + bias;
         const float dlt = p.delta_softplus ? softplus_f32(v) : v;
         const float dx = dlt * x;
-        float acc = 0.0f;
+        float acc[N], cv[N];
 #pragma unroll
         for (int n = 0; n < N; ++n) {
             const float abar = hw_exp2(dlt * a2[n]);                         // ZOH on A
             const float bx = dx * Act<IN>::ld(p.Bm, bc + n * L + t);         // Euler on B
             h[n] = __builtin_fmaf(abar, h[n], bx);
-            acc = __builtin_fmaf(Act<IN>::ld(p.Cm, bc + n * L + t), h[n], acc);
+            cv[n] = Act<IN>::ld(p.Cm, bc + n * L + t);
         }
-        float yv = __builtin_fmaf(dskip, x, acc);
+        // The sum over states in the order in which the ring kernel forms it in a sequence's last
+        // timesteps: a pair per lane, then pairs of pairs.
+#pragma unroll
+        for (int n = 0; n < N; n += 2) acc[n] = N == 1 ? cv[n] * h[n] : __builtin_fmaf(cv[n + 1], h[n + 1], cv[n] * h[n]);
+#pragma unroll
+        for (int w = 2; w < N; w *= 2)
+#pragma unroll
+            for (int n = 0; n < N; n += 2 * w) acc[n] += acc[n + w];
+        float yv = __builtin_fmaf(dskip, x, acc[0]);
         if (p.z) yv *= silu_f32(Act<IN>::ld(p.z, base + t));
         st_out<OUT>(p.y, base + t, yv);
         for (int64_t k = 0; k < p.npos; ++k) {          // states at requested positions

@@ -34,9 +34,10 @@ def _exe() -> str:
     return exe
 
 
-def plans(shapes, *, dstate=16, dtype="bf16", out_bytes=4, gate=True, aligned=True, ckpt=False, cus=256):
+def plans(shapes, *, dstate=16, dtype="bf16", out_bytes=4, gate=True, aligned=True, ckpt=False,
+          npos=0, h0=False, cus=256):
     lines = "".join(f"{b} {d} {L} {dstate} {2 if dtype == 'bf16' else 4} {out_bytes} {int(gate)} {int(aligned)} "
-                    f"{int(ckpt)} {cus}\n" for b, d, L in shapes)
+                    f"{int(ckpt)} {npos} {int(h0)} {cus}\n" for b, d, L in shapes)
     out = subprocess.run([_exe()], input=lines, check=True, capture_output=True, text=True).stdout
     return [Plan(w[0], *map(int, w[1:])) for w in (line.split() for line in out.splitlines())]
 

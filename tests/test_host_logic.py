@@ -23,8 +23,9 @@ def test_every_problem_fits_its_launch(L, chains):
         assert p.workgroups * (p.threads // 64) >= chains * p.waves
     else:
         assert p.kernel == "row" and p.workgroups * p.threads >= 8 * chains
-    # one wave per chain fits below 2^26 chains
-    assert (p.kernel == "ring") == (chains < 2 ** 26)
+    # one wave per chain fits below 2^26 chains; the row kernel takes a timestep or two of many
+    assert (p.kernel == "ring") == (chains < 2 ** 26 and L > 1)
+    assert plan((chains, 8, L), h0=True).kernel == ("ring" if chains < 2 ** 26 else "row")
     aligned16 = plan((1, 8 * chains, 16))
     assert aligned16.workgroups * aligned16.threads <= U32, aligned16
 
@@ -97,6 +98,21 @@ def test_chunk_kernel_where_it_is_faster():
     assert plan((16, 3584, 1009), dtype="f32", aligned=True).kernel == "ring"
     segmented = plan((1, 1280, 65536), dtype="f32")
     assert segmented[:4] == ("chunk", 25, 2624, 1) and segmented.workgroups == 25 * 160 // 4
+
+
+def test_row_kernel_for_a_few_timesteps_of_many_rows():
+    """Without a first state or positions: bf16 up to 8 timesteps, from 16 chains per compute unit and 16 more per
+    timestep; fp32 up to 4, from 8 and 24 more."""
+    cu = 256
+    for L in range(1, 12):
+        for dtype, least in (("bf16", 16 + 16 * L if L <= 8 else None), ("f32", 8 + 24 * L if L <= 4 else None)):
+            edge = (least or 1000) * cu
+            below, at = plans([(edge - 1, 8, L), (edge, 8, L)], dtype=dtype)
+            assert (below.kernel, at.kernel) == ("ring", "row" if least else "ring"), (L, dtype)
+            if at.kernel == "row":
+                assert at.workgroups * at.threads == 8 * edge and at.threads == 64 and at.nseg == 1
+            for kw in (dict(h0=True), dict(npos=1)):
+                assert plan((edge, 8, L), dtype=dtype, **kw).kernel == "ring"
 
 
 def test_waves_per_chain():
