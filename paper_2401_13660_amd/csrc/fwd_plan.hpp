@@ -140,24 +140,54 @@ inline int64_t chunk_segments(int64_t chains, int64_t L, int64_t cus, int64_t *s
     return (L + len - 1) / len;
 }
 
-// The chunk kernel takes whole slices in aligned rows where the problem moves more bytes than
-// the 256 MB of the Infinity Cache hold and it is the faster one.  In us, ring and chunk:
-// - fp32 in, from 7 chains per CU, (4, 3584, 2048) 153 and 145, (16, 3584, 1024) 318 and 263
-//   ((4, 3072, 2048), 6 per CU, 132 and 140; (16, 3584, 256), 235 MB, 70 and 67); with
-//   checkpoints from 6, (4, 3072, 2048) 154 and 146, (2, 4608, 2048), 4.5 per CU, 127 and 142;
-// - fp32 in, few chains, which both cut into segments: from 1/4 to 7/8 of a chain per CU, (1,
-//   1280, 65536) 700 and 631, (1, 512, 65536) 293 and 286, (1, 256, 65536) 160 and 176, (1,
-//   1792, 65536) 819 and 883; and up to 1.2, (1, 2112, 16384) 307 and 268, (1, 2688, 16384)
-//   315 and 326;
-// - bf16 in, with checkpoints, from 16 chains per CU: (16, 3584, 512) 150 and 138, (64, 3584,
-//   256) 327 and 299, (8, 3584, 2048) 290 either way.
+// The chunk kernel takes whole slices in aligned rows where it is the faster one: where a
+// problem moves more bytes than the 256 MB of the Infinity Cache hold, or where its one wave
+// per chain, 8 per CU at a time, fills the chip evenly.  In rows of an odd number of slices its
+// loads of 32 timesteps straddle lines, and some of the rules leave those out.  In us, ring and
+// chunk:
+// - fp32 in, rounds of 8 chains per CU at least 7/8 full, even rows of 192 timesteps and more,
+//   of any size: (4, 4096, 384) 34.1 and 30.7, (16, 4096, 256) 85 and 77, (4, 3840, 1024) 79
+//   and 71; without recorded positions, for which this kernel takes a launch more;
+// - fp32 in, more than 256 MB, above 6 chains per CU, rounds of 8 at least 5/8 full: (3, 4608,
+//   2048) 164 and 145, (4, 3072, 2048), 6 exactly, 140 either way, (5, 3584, 8160) with
+//   checkpoints, 8.75, 901 and 953, without a gate (5, 3584, 11072) 948 and 1084;
+// - the same with checkpoints, also above 3 and up to 4: (4, 2048, 2304) 125 and 113, (1, 6144,
+//   8160), 3 exactly, 320 and 377; and in even rows above 5: (1, 10648, 5632) 413 and 387, (2,
+//   5632, 2640) 202 and 215;
+// - bf16 in, with checkpoints, more than 256 MB: above 16 chains per CU, (16, 3584, 512) 150 and
+//   138, (64, 3584, 256) 327 and 299; and above 4 where rounds of 4 chains per CU are at least
+//   7/8 full, (8, 2048, 8160) 715 and 606, (7, 4608, 2304) 382 and 338, (5, 3584, 8160), 8.75
+//   per CU, 782 and 880; with bf16 out 15/16, (8, 3072, 2304) 268 and 251, (7, 4096, 1024), 14
+//   per CU, 138 and 144; from 192 timesteps, (91, 4608, 64) 162 and 183;
+// - where states are recorded only with 128 timesteps for each, as it runs up to 32 timesteps
+//   again for one: fp32 (38, 6304, 80) with 16 positions 459 and 616;
+// - fp32 in, more than 256 MB beside the checkpoints, few chains, which both cut into segments:
+//   from 1/4 to 7/8 of a chain per CU, (1, 1280, 65536) 700 and 631, (1, 512, 65536) 293 and 286,
+//   (1, 1792, 65536) 819 and 883, of more than 768 MB from 1/8, (1, 256, 468736) 1092 and 1021;
+//   and above 1, up to 1.2, (1, 2112, 16384) 307 and 268, (1, 2688, 16384) 315 and 326.
+// The two kernels give the same bits except where they cut a sequence into other segments, and
+// storing checkpoints or recording positions must not change them: only the last rule chooses
+// for a problem that is cut, and it asks for neither.
 inline bool chunk_is_faster(const Shape &s, int64_t chains, int64_t cus) {
     if (!s.aligned16 || s.L % kSlice != 0) return false;
-    const int64_t per_step = s.in_bytes * (s.gate ? 3 : 2) + s.out_bytes + (s.ckpt ? 4 : 0);
-    if (s.batch * s.dim <= (int64_t(256) << 20) / (s.L * per_step)) return false;
-    if (s.in_bytes == 2) return s.ckpt && chains > 16 * cus;
-    if (chains > cus) return chains * 5 <= cus * 6 || chains >= (s.ckpt ? 6 : 7) * cus;
-    return chains * 4 >= cus && chains * 8 < cus * 7;
+    const bool even = s.L % 32 == 0;
+    const int64_t per_step = s.in_bytes * (s.gate ? 3 : 2) + s.out_bytes;
+    auto moves_more_than = [&](int64_t mib, int64_t bytes) { return s.batch * s.dim > (mib << 20) / (s.L * bytes); };
+    // do the chains fill num/den of their rounds of k per CU?
+    auto filled = [&](int64_t k, int64_t num, int64_t den) {
+        const int64_t round = k * cus, rounds = (chains + round - 1) / round;
+        return chains * den >= rounds * round * num;
+    };
+    if (chains <= 3 * cus) {
+        if (s.in_bytes == 2 || !moves_more_than(256, per_step)) return false;
+        if (chains < cus) return chains * (moves_more_than(768, per_step) ? 8 : 4) >= cus && chains * 8 < cus * 7;
+        return chains > cus && chains * 5 <= cus * 6;
+    }
+    if (s.in_bytes == 4 && s.npos == 0 && even && s.L >= 192 && filled(8, 7, 8)) return true;
+    if (!moves_more_than(256, per_step + (s.ckpt ? 4 : 0)) || s.L < 128 * s.npos) return false;
+    if (s.in_bytes == 2)
+        return s.ckpt && s.L >= 192 && (chains > 16 * cus || (chains > 4 * cus && (s.out_bytes == 4 ? filled(4, 7, 8) : filled(4, 15, 16))));
+    return (chains > 6 * cus && filled(8, 5, 8)) || (s.ckpt && (chains <= 4 * cus || (even && chains > 5 * cus)));
 }
 
 // The row kernel takes a few timesteps of many rows that start from zero: a wave of the ring

@@ -1,7 +1,7 @@
 """The forward's chunk kernel: what it computes is what the ring kernel computes, bit for bit.
 
-The chunk kernel takes large problems (more than 256 MB moved) with many chains of 8 channels,
-or few enough to be cut into time segments.  Uncut, its states and outputs come from the ring
+The chunk kernel takes problems of many chains of 8 channels, or of few enough to be cut into time
+segments, most of them of more than 256 MB.  Uncut, its states and outputs come from the ring
 kernel's operations in the same order, so a batch element must have the bits that it has in a
 small batch, which the ring kernel takes; cut, its segments are others than the ring kernel's,
 and sampled rows are held to the fp64 oracle (2e-3 on y, 1e-4 on states).
@@ -18,13 +18,15 @@ from test_gpu_positions import check_states
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not has_gpu(), reason="needs a GPU")]
 
 
-# (dim, L, copies): an odd number of 16-timestep slices and an even one; dead lanes
-@pytest.mark.parametrize("dtype,entry", [("f32", "fwd"), ("f32", "states"), ("f32", "ckpt"), ("bf16", "ckpt")])
-@pytest.mark.parametrize("L,gated,out_dtype", [(368, True, torch.float32), (512, False, torch.bfloat16)])
-def test_same_bits_as_the_ring_kernel(dtype, entry, L, gated, out_dtype):
+# an odd number of 16-timestep slices and an even one; dead lanes; 128 timesteps and more for each of 7 positions
+@pytest.mark.parametrize("dtype,entry,L", [("f32", "fwd", 368), ("f32", "fwd", 512), ("f32", "states", 912), ("f32", "states", 1024),
+                                           ("f32", "ckpt", 368), ("f32", "ckpt", 512), ("bf16", "ckpt", 368), ("bf16", "ckpt", 512)])
+def test_same_bits_as_the_ring_kernel(dtype, entry, L):
     import paper_2401_13660_amd as mb
     dim, n = 2045, 32                                    # 256 chains each: 8,192
-    kw = dict(dtype=dtype, gate=gated, out_bytes=2 if out_dtype == torch.bfloat16 else 4, ckpt=entry == "ckpt")
+    gated, out_dtype = (True, torch.float32) if L in (368, 912) else (False, torch.bfloat16)
+    kw = dict(dtype=dtype, gate=gated, out_bytes=2 if out_dtype == torch.bfloat16 else 4, ckpt=entry == "ckpt",
+              npos=7 if entry == "states" else 0, h0=True)
     assert plan((1, dim, L), **kw).kernel == "ring" and plan((n, dim, L), **kw).kernel == "chunk"
     inp = make_inputs(1, dim, L, 16, dtype=dtype, seed=L, gated=gated, with_h0=True)
     t = to_device(inp)
@@ -58,7 +60,7 @@ def test_same_bits_as_the_ring_kernel(dtype, entry, L, gated, out_dtype):
 def test_segments(shape, entry):
     import paper_2401_13660_amd as mb
     nb, dim, L = shape
-    p = plan(shape, dtype="f32", ckpt=entry == "ckpt")
+    p = plan(shape, dtype="f32", ckpt=entry == "ckpt", npos=7 if entry == "states" else 0, h0=True)
     assert p.kernel == "chunk" and p.nseg > 8, p
     inp = make_inputs(nb, dim, L, 16, dtype="f32", seed=5, with_h0=True)
     rows = np.unique(np.concatenate([np.arange(0, dim, dim // 40), [dim - 1]]))

@@ -69,33 +69,69 @@ def test_segments_follow_the_rule():
 
 def test_every_carry_fits_the_allocation_free_array():
     """On 256 compute units no carry exceeds the allocation-free call's 8 MiB."""
-    shapes = [(1, 8 * c, L) for c in range(1, 400) for L in (2048, 4096, 8192, 16384, 20480, 32768, 65536, 2 ** 24)]
+    shapes = [(1, 8 * c, L) for c in range(1, 1025) for L in (2048, 4096, 8192, 16384, 20480, 32768, 65536, 2 ** 24)]
     for dtype in ("bf16", "f32"):
         assert 4 << 20 < max(p.carry for p in plans(shapes, dtype=dtype)) <= 8 << 20
 
 
-def test_chunk_kernel_where_it_is_faster():
-    """fp32 and, with checkpoints, bf16 problems of more than 256 MB whose chains are many, or few
-    enough to be cut; whole slices in aligned rows only."""
-    mb256 = 256 << 20
+def _kernel(chains, mib, odd=False, **kw):
+    """The kernel of the shortest sequence in whole lines (or an odd number of slices) of more than `mib` MiB."""
+    kw = {"dtype": "f32", "out_bytes": 4, **kw}
+    per = 3 * (4 if kw["dtype"] == "f32" else 2) + kw["out_bytes"] + (4 if kw.get("ckpt") else 0)
+    L = ((mib << 20) // (8 * chains * per * 32) + 1) * 32
+    return plan((1, 8 * chains, L - 16 if odd else L), **kw).kernel
 
-    def kernel(chains, nbytes, **kw):                    # the length that just passes, or not
-        kw = {"dtype": "f32", **kw}
-        per = (8 if kw["dtype"] == "bf16" else 16) + (4 if kw.get("ckpt") else 0) + (2 if kw["dtype"] == "bf16" else 0)
-        L = (nbytes // (8 * chains * per * 16) + (nbytes > mb256)) * 16
-        return plan((1, 8 * chains, L), **kw).kernel
 
-    more, less = mb256 + 1, mb256
-    for chains, want in {63: "ring", 64: "chunk", 223: "chunk", 224: "ring", 256: "ring", 257: "chunk", 307: "chunk",
-                         308: "ring", 1791: "ring", 1792: "chunk", 28672: "chunk"}.items():
-        assert kernel(chains, more) == want, chains
-        assert kernel(chains, less) == "ring", chains
-        assert kernel(chains, more, aligned=False) == "ring"
-    assert [kernel(c, more, ckpt=True) for c in (1535, 1536)] == ["ring", "chunk"]
-    bf = dict(dtype="bf16")
-    assert plan((16, 3584, 512), **bf).kernel == "ring"
-    assert [plan(s, ckpt=True, **bf).kernel for s in ((16, 3584, 512), (16, 3584, 320), (8, 3584, 2048))] == ["chunk", "ring", "ring"]
-    assert plan((16, 3584, 1009), dtype="f32", aligned=True).kernel == "ring"
+def _chunk_ranges(mib, last, **kw):
+    """The ranges of chains that the chunk kernel takes, first and last of each."""
+    found, prev = [], False
+    for c in range(1, last + 2):
+        now = c <= last and _kernel(c, mib, **kw) == "chunk"
+        if now and not prev:
+            found.append([c])
+        if prev and not now:
+            found[-1].append(c - 1)
+        prev = now
+    return [tuple(f) for f in found]
+
+
+# 256 compute units; (mib + 32, odd) rather than mib where an odd number of slices would fall below it
+@pytest.mark.parametrize("want,mib,kw", [
+    ([(64, 223), (257, 307), (1537, 1700)], 256, {}),
+    ([(64, 223), (257, 307), (1537, 1700)], 320, dict(odd=True)),
+    ([(64, 223), (257, 307), (1537, 1700)], 256, dict(npos=1)),
+    ([(64, 223), (257, 307)], 256, dict(npos=40)),
+    ([(32, 223), (257, 307)], 768, {}),
+    ([(64, 223), (257, 307), (769, 1024), (1281, 1700)], 320, dict(ckpt=True)),
+    ([(64, 223), (257, 307), (769, 1024), (1537, 1700)], 400, dict(ckpt=True, odd=True)),
+    ([], 256, dict(dtype="bf16")),
+    ([], 768, dict(dtype="bf16", ckpt=True)),
+    ([], 320, dict(aligned=False, ckpt=True)),
+])
+def test_chunk_kernel_where_it_is_faster(want, mib, kw):
+    last = 1700 if any(hi == 1700 for _, hi in want) else 700
+    assert _chunk_ranges(mib, last, **kw) == want
+
+
+def test_chunk_kernel_where_chains_fill_the_chip():
+    """fp32 of any size from 192 timesteps where rounds of 2,048 chains are 7/8 full; bf16 with checkpoints
+    where rounds of 1,024 are, and from 4,097 chains; nothing else below 256 MB."""
+    f32 = dict(dtype="f32")
+    for chains, want in {1791: "ring", 1792: "chunk", 2048: "chunk", 2049: "ring", 3583: "ring", 3584: "chunk", 4096: "chunk",
+                         4097: "ring"}.items():
+        assert plan((1, 8 * chains, 192), **f32).kernel == want, chains
+        assert plan((1, 8 * chains, 192), ckpt=True, **f32).kernel == want, chains
+        for other in (dict(dtype="f32", npos=1), dict(dtype="f32", aligned=False), dict(dtype="bf16", ckpt=True)):
+            assert plan((1, 8 * chains, 192), **other).kernel == "ring"
+        assert {plan((1, 8 * chains, L), **f32).kernel for L in (160, 200, 208)} == {"ring"}
+    ck = dict(dtype="bf16", ckpt=True)
+    for c, f32_out, bf16_out in ((1024, "ring", "ring"), (1791, "ring", "ring"), (1792, "chunk", "ring"), (1919, "chunk", "ring"),
+                                 (1920, "chunk", "chunk"), (2048, "chunk", "chunk"), (2049, "ring", "ring"), (2687, "ring", "ring"),
+                                 (2688, "chunk", "ring"), (2880, "chunk", "chunk"), (3073, "ring", "ring"), (4096, "chunk", "chunk"),
+                                 (4097, "chunk", "chunk"), (8000, "chunk", "chunk")):
+        assert (_kernel(c, 256, **ck), _kernel(c, 256, out_bytes=2, **ck)) == (f32_out, bf16_out), c
+        assert _kernel(c, 256, dtype="bf16") == "ring"
+        assert c > 4097 or _kernel(c, 200, **ck) == "ring"
     segmented = plan((1, 1280, 65536), dtype="f32")
     assert segmented[:4] == ("chunk", 25, 2624, 1) and segmented.workgroups == 25 * 160 // 4
 
@@ -113,6 +149,27 @@ def test_row_kernel_for_a_few_timesteps_of_many_rows():
                 assert at.workgroups * at.threads == 8 * edge and at.threads == 64 and at.nseg == 1
             for kw in (dict(h0=True), dict(npos=1)):
                 assert plan((edge, 8, L), dtype=dtype, **kw).kernel == "ring"
+
+
+def test_recording_changes_no_cut():
+    """mb_scan_fwd_states and mb_scan_fwd_ckpt give mb_scan_fwd's bits: the ring and the chunk kernel may
+    stand in for each other where neither cuts the sequence, the row kernel too for sequences of less than a
+    slice; any two plans that cut must be alike."""
+    shapes = [(1, 8 * c, L) for c in (1, 8, 31, 33, 63, 64, 100, 200, 223, 224, 256, 257, 288, 300, 307, 341, 358, 400, 513, 576, 700, 768,
+                                      769, 1024, 1400, 2048, 3000, 4096, 5000)
+              for L in (1, 4, 48, 512, 2048, 4096, 8192, 16384, 32768, 65536, 131072, 2 ** 20)]
+    shapes += [(65536, 8, L) for L in (1, 2, 3, 4, 8, 9)]
+    for dtype in ("bf16", "f32"):
+        for out_bytes in (2, 4):
+            kw = dict(dtype=dtype, out_bytes=out_bytes)
+            plain = plans(shapes, **kw)
+            for other in (plans(shapes, npos=1, **kw), plans(shapes, npos=40, **kw), plans(shapes, ckpt=True, **kw)):
+                for shape, p, o in zip(shapes, plain, other):
+                    if o.kernel != p.kernel:
+                        assert {p.kernel, o.kernel} == {"ring", "chunk" if shape[2] >= 16 else "row"}, (shape, p, o)
+                    assert p[1:4] == o[1:4], (shape, p, o)
+                    assert p.nseg == 1 or p.kernel == o.kernel, (shape, p, o)
+    assert {p.kernel for p in plain} == {"row", "ring", "chunk"}
 
 
 def test_waves_per_chain():
