@@ -70,8 +70,8 @@ inline int64_t ring_workgroups(int64_t chains, uint32_t log_w) {
 inline uint32_t waves_per_chain_log2(int64_t chains, int64_t slices, int64_t cus) {
     uint32_t lw = chains <= cus ? 3 : 2;
     if (chains > 4 * cus && slices <= 16)
-        lw = slices <= 4 || (slices <= 8 && chains >= 7 * cus) || chains > 16 * cus ? 0 : 1;
-    else if ((chains > 3 * cus && slices <= 8) || (chains > 8 * cus && slices <= 32))
+        lw = slices <= 4 || (slices <= 8 && chains >= 7 * cus) || chains > 24 * cus ? 0 : 1;
+    else if ((chains > 3 * cus && slices <= 8) || (chains > 11 * cus && slices <= 32))
         lw = 1;
     while (lw > 0 && ((int64_t(1) << lw) > slices || !launch_fits(ring_workgroups(chains, lw), ring_threads(lw)))) --lw;
     return lw;
@@ -99,7 +99,9 @@ inline uint32_t waves_per_chain_log2(int64_t chains, int64_t slices, int64_t cus
 // most 4 waves per SIMD, of at least 512 and 768 timesteps: (1, 1024, 32768), 8 segments in
 // 1, 2 and 4 pieces, 271, 249 and 248; (1, 1536, 16384), 5 segments in 2 and 4, 189 and 164;
 // (1, 512, 8192), 16 segments of 512 timesteps in 1 and 2, 44 and 47; (1, 512, 32768), 16 of
-// 2048 in 2 and 4, 125 and 128.
+// 2048 in 2 and 4, 125 and 128.  Shorter ones into 2 while there are at most 16 of them and that
+// makes no more than one wave per SIMD: (1, 512, 2048), 8 of 256, 21.8 and 19.2; (1, 320, 4096),
+// 16 of 256, 23.2 and 22.6, (1, 640, 4096), 16, 25.9 and 26.4, (1, 80, 6144), 24, 23.5 and 24.1.
 inline int64_t segments(int64_t chains, int64_t L, int64_t cus, int64_t *seg_len, int64_t *pieces) {
     int64_t n = 1, m = 1;
     const int64_t least_L = chains * 8 <= cus * 4 ? 2048 : chains * 8 <= cus * 5 ? 3072
@@ -114,6 +116,7 @@ inline int64_t segments(int64_t chains, int64_t L, int64_t cus, int64_t *seg_len
     if (n <= 1) return 1;
     const int64_t least = (L + n - 1) / n;
     while (m < 4 && 2 * m * chains * (n - 1) <= 16 * cus && least >= (m == 1 ? 1024 : 3072)) m *= 2;
+    if (m == 1 && n <= 16 && 2 * chains * (n - 1) <= 4 * cus) m = 2;
     const int64_t unit = 32 * m;                        // pieces of a multiple of 32 timesteps
     const int64_t len = (least + unit - 1) / unit * unit;
     *seg_len = len;

@@ -194,8 +194,9 @@ def test_h_last_may_alias_h0_segmented(shape, entry):
 def test_same_bits_with_any_number_of_waves(dtype, out_dtype, gated, with_h0, softplus):
     import paper_2401_13660_amd as mb
     dim, L = 2045, 256                                   # 256 chains, dead lanes
-    copies = {1: 8, 2: 4, 5: 2, 17: 1}                   # batch: waves per chain
-    assert {n: plan((n, dim, L)).waves for n in copies} == copies
+    copies = {1: 8, 2: 4, 5: 2, 25: 1}                   # batch: waves per chain
+    plans = {n: plan((n, dim, L), dtype=dtype) for n in copies}
+    assert {n: p.waves for n, p in plans.items()} == copies and {p.kernel for p in plans.values()} == {"ring"}
     inp = make_inputs(1, dim, L, 16, dtype=dtype, seed=31, gated=gated, with_h0=with_h0, with_bias=softplus)
     if not softplus:
         # used as given, Delta must stay positive (else abar > 1 and the state grows without bound)
@@ -246,18 +247,17 @@ def test_deterministic():
 
 
 # Segments of 256 timesteps and of 512, the last one shorter, dead lanes; the pre-pass in one
-# piece per segment and in two (the last two); few chains and just over one per compute unit
-# (the last).
-@pytest.mark.parametrize("shape", [(1, 64, 4096), (1, 61, 4112), (2, 24, 8192), (1, 8, 2080), (1, 509, 16400),
-                                   (1, 2108, 8208)])
+# piece per segment and in two; few chains and just over one per compute unit (the last).
+@pytest.mark.parametrize("shape,pieces", [((1, 64, 4096), 2), ((1, 61, 4112), 2), ((1, 61, 8208), 1), ((2, 24, 8192), 1),
+                                          ((1, 8, 2080), 2), ((1, 509, 16400), 2), ((1, 2108, 8208), 2)])
 @pytest.mark.parametrize("gated", [True, False])
-def test_time_segments(shape, gated):
+def test_time_segments(shape, pieces, gated):
     """Few (batch, channel) rows and a long sequence: time is cut into segments, a pre-pass
     computes each segment's aggregate (in one or two pieces per segment) and the scan folds
     them."""
     nb, dim, L = shape
     p = plan(shape)
-    assert p.nseg > 1 and p.pieces == (2 if dim > 500 else 1), p
+    assert p.nseg > 1 and p.pieces == pieces, p
     inp = make_inputs(nb, dim, L, 16, dtype="bf16", seed=15, with_h0=True, gated=gated, A_kind="random")
     announce(f"time segments {shape} gated={gated}")
     run_case(inp)

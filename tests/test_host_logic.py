@@ -41,7 +41,7 @@ def _rule(chains: int, L: int):
     if n <= 1:
         return 1, None, 1
     least = -(-L // n)
-    m = 1
+    m = 2 if n <= 16 and 2 * chains * (n - 1) <= 1024 else 1
     if least >= 1024 and 2 * chains * (n - 1) <= 4096:
         m = 4 if least >= 3072 and 4 * chains * (n - 1) <= 4096 else 2
     seg = -(-least // (32 * m)) * (32 * m)
@@ -60,7 +60,7 @@ def test_segments_follow_the_rule():
             assert p.seg_len == seg and seg % (32 * m) == 0 and seg >= 256
             assert (n - 1) * seg < L <= n * seg
     # worked by hand: segments, length, pieces
-    hand = {(1, 8, 65536): (128, 512, 1), (1, 64, 2048): (8, 256, 1), (1, 512, 16384): (16, 1024, 2),
+    hand = {(1, 8, 65536): (128, 512, 1), (1, 64, 2048): (8, 256, 2), (1, 584, 2048): (8, 256, 2), (1, 592, 2048): (8, 256, 1), (1, 80, 4352): (17, 256, 1), (1, 512, 16384): (16, 1024, 2),
             (1, 1024, 32768): (8, 4096, 4), (1, 1528, 20480): (5, 4096, 4), (1, 1536, 16384): (5, 3328, 4), (1, 1528, 4095): (1, None, 1),
             (1, 2304, 8192): (8, 1024, 2), (1, 2304, 8191): (1, None, 1), (1, 2312, 8192): (1, None, 1), (2, 24, 8192): (32, 256, 1)}
     for (shape, want), p in zip(hand.items(), plans(list(hand), aligned=False)):
@@ -179,6 +179,6 @@ def test_waves_per_chain():
             (768, 128): 4, (769, 128): 2, (769, 129): 4, (1024, 64): 2, (1024, 129): 4,
             (1025, 64): 1, (1025, 65): 2, (1025, 256): 2, (1025, 257): 4,
             (1791, 128): 2, (1792, 128): 1, (1792, 129): 2, (2048, 257): 4,
-            (2049, 257): 2, (2049, 512): 2, (2049, 513): 4, (4096, 256): 2, (4097, 256): 1, (4097, 257): 2}
+            (2816, 257): 4, (2817, 257): 2, (2817, 512): 2, (2817, 513): 4, (6144, 256): 2, (6145, 256): 1, (6145, 257): 2}
     got = plans([(1, 8 * c, L) for c, L in want], aligned=False)
     assert {k: p.waves for k, p in zip(want, got)} == want
