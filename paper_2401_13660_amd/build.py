@@ -1,7 +1,7 @@
 """Build the HIP library libmbscan.so in-tree (gfx950 only), the binding's native entry
 points (csrc/fastcall.cpp), the issue-rate
 micro-benchmark behind the instruction cost model (csrc/issue_rates.hip), the
-LDS bank probe behind the time-split kernel's tables (csrc/lds_banks.hip), and
+LDS bank probe behind the layout of the kernels' tables (csrc/lds_banks.hip), and
 the exhaustive check of the bf16 pair conversion (csrc/bf16_pack_check.hip).
 
     python -m paper_2401_13660_amd.build
@@ -95,7 +95,7 @@ def build_issue_rates(verbose: bool = False) -> str:
 
 
 def build_lds_banks(verbose: bool = False) -> str:
-    """The LDS bank probe behind the time-split kernel's table layout (./lds_banks)."""
+    """The LDS bank probe behind the layout of the kernels' tables (./lds_banks)."""
     return build_tool("lds_banks", verbose)
 
 

@@ -11,9 +11,8 @@
 // same program under rocprofv3 --pmc (dispatch 1 is a warm-up, dispatch n + 1 the
 // table's row n).
 //
-// Patterns: strided lanes and groups of consecutive lanes (the bank rules), and
-// every LDS access of the time-split forward kernel, in the table layout it had
-// first ("old") and in the one laid out by these rules ("new").
+// Patterns: strided lanes and groups of consecutive lanes, from which come the bank
+// rules that the kernels' tables follow.
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -89,35 +88,6 @@ void add(std::vector<Pattern> &v, const std::string &name, bool write, int nb,
     v.push_back(p);
 }
 
-// The time-split kernel's tables: lane l = 16 j + 2 q + k (channel j, state pair
-// q, slice k); 16-byte entries.  Layout: bc row stride and slice pad, dd row
-// stride and slice pad, part row stride.
-struct Ts2Layout { int s_bc, pad_bc, s_dd, pad_dd, p; };
-
-void add_ts2(std::vector<Pattern> &v, const char *tag, Ts2Layout y) {
-    auto J = [](int l) { return l >> 4; };
-    auto Q = [](int l) { return (l >> 1) & 7; };
-    auto K = [](int l) { return l & 1; };
-    auto bc = [&](int t) { return y.s_bc * t + (t >= 16 ? y.pad_bc : 0); };
-    auto dd = [&](int r) { return y.s_dd * r + (r >= 8 ? y.pad_dd : 0); };
-    auto mk = [&](const std::string &name, bool write, int nb, const std::function<unsigned(int)> &addr) {
-        add(v, std::string(tag) + " " + name, write, nb, addr);
-    };
-    mk("dd write", true, 16, [&](int l) { return (unsigned)(dd(8 * K(l) + Q(l)) + J(l)) * 16; });
-    for (int i = 0; i < 4; ++i)
-        mk("bc write " + std::to_string(i), true, 16, [&](int l) { return (unsigned)(bc(4 * (2 * J(l) + K(l)) + i) + Q(l)) * 16; });
-    for (int tq = 0; tq < 4; ++tq) {
-        for (int i = 0; i < 2; ++i)
-            mk("dd read " + std::to_string(2 * tq + i), false, 16, [&](int l) { return (unsigned)(dd(8 * K(l) + 2 * tq + i) + J(l)) * 16; });
-        for (int i = 0; i < 4; ++i)
-            mk("bc read " + std::to_string(4 * tq + i), false, 16, [&](int l) { return (unsigned)(bc(16 * K(l) + 4 * tq + i) + Q(l)) * 16; });
-        mk("part write " + std::to_string(tq), true, 16, [&](int l) { return (unsigned)((8 * J(l) + 4 * K(l) + tq) * y.p + Q(l)) * 16; });
-    }
-    for (int w = 0; w < 8; ++w)
-        mk("partial read " + std::to_string(w), false, 8,
-           [&](int l) { return (unsigned)((8 * J(l) + 4 * K(l) + (Q(l) >> 1)) * y.p * 16 + (2 * w + (Q(l) & 1)) * 8); });
-}
-
 bool ok(hipError_t e, const char *what) {
     if (e == hipSuccess) return true;
     std::fprintf(stderr, "%s: %s\n", what, hipGetErrorString(e));
@@ -140,8 +110,6 @@ int main() {
                     [=](int l) { return (unsigned)((l % g) * nb + 1024 * (l / g)); });
         }
     }
-    add_ts2(pats, "time-split, old:", Ts2Layout{10, 8, 5, 0, 10});
-    add_ts2(pats, "time-split, new:", Ts2Layout{9, 8, 5, 4, 9});
     for (const Pattern &p : pats)
         for (unsigned x : p.a)
             if (x % p.nb || x + p.nb > (unsigned)kRegion) {
