@@ -37,20 +37,17 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, 8 TB/s
 #    cycle; one wave alone issues one about every 7 cycles), and only when no
 #    operand is an SGPR and the two multiplicand VGPRs of a multiply-add differ in
 #    parity (index mod 2);
-#  - with one transcendental per four other instructions, as in the scan, and 2
-#    waves per SIMD (the scan's occupancy), the mix averages 5.0 cycles per
-#    instruction: 8.6 for the exponential and 4.1 for each of the others.
-# Per element the forward needs at least 76 VALU and 20 transcendental
-# lane-operations: per state dlt * A, its exponential, dlt * u * B, the state FMA
-# and the C FMA (64 + 16), and per element softplus (exp, log), silu (exp, rcp) and
-# about 12 VALU operations.  At those rates and 2.4 GHz that is 7.6 SIMD-cycles per
+#  - beside transcendentals the others issue singly, at 4.0-4.4 cycles; an MFMA of the
+#    forward's kind (v_mfma_f32_4x4x1) takes 8.1 and overlaps with none of them.
+# The forward kernel issues, per slice of 128 elements (its counters), 40 transcendentals, 12
+# MFMAs and 171 other VALU instructions: at 8, 8 and 4 cycles 1,100, or 8.6 SIMD-cycles per
 # element.
+FWD_SIMD_CYCLES_PER_ELEMENT = (40 * 8 + 12 * 8 + 171 * 4) / 128.0
+ALU_PEAK_GELEMS = 1024 * 2.4e9 / FWD_SIMD_CYCLES_PER_ELEMENT / 1e9
+# The backward by a count of its least operations, at 2 waves per SIMD.
 VALU_CYCLES, TRANS_CYCLES = 4.1, 8.6
-ALU_SIMD_CYCLES_PER_ELEMENT = (76 * VALU_CYCLES + 20 * TRANS_CYCLES) / 64.0
-ALU_PEAK_GELEMS = 1024 * 2.4e9 / ALU_SIMD_CYCLES_PER_ELEMENT / 1e9
-# The same model for the backward (the gradients of eq. (2) by reverse-mode
-# differentiation), per element.  Per state: the forward recomputed (dlt * A, the
-# exponential, dlt * u * B, the state FMA), lambda and its carry (2), dB and dC
+# The gradients of eq. (2) by reverse-mode differentiation, per element.  Per state:
+# the forward recomputed (dlt * A, the exponential, dlt * u * B, the state FMA), lambda and its carry (2), dB and dC
 # (a product and a sum over channels each: 4), sum_n lambda B (1), the decay term
 # lambda abar h_{t-1} with its A-weighted sum and the dA sum (3) and C . h for dz
 # (1): 14 VALU + 1 transcendental.  Per element at least 5 transcendentals
@@ -58,7 +55,7 @@ ALU_PEAK_GELEMS = 1024 * 2.4e9 / ALU_SIMD_CYCLES_PER_ELEMENT / 1e9
 # operations (ds, dz, du, ddelta, the dDskip and dbias sums, dlt * u).
 BWD_SIMD_CYCLES_PER_ELEMENT = ((16 + 5) * TRANS_CYCLES + (16 * 14 + 16) * VALU_CYCLES) / 64.0
 BWD_ALU_PEAK_GELEMS = 1024 * 2.4e9 / BWD_SIMD_CYCLES_PER_ELEMENT / 1e9
-TRAIN_ALU_PEAK_GELEMS = 1024 * 2.4e9 / (ALU_SIMD_CYCLES_PER_ELEMENT + BWD_SIMD_CYCLES_PER_ELEMENT) / 1e9
+TRAIN_ALU_PEAK_GELEMS = 1024 * 2.4e9 / (FWD_SIMD_CYCLES_PER_ELEMENT + BWD_SIMD_CYCLES_PER_ELEMENT) / 1e9
 METRIC = "selective-scan GB/s & %HBM peak (972M layer, L=8192); B·L·D elems/s"
 DEFAULT_WORKLOAD = "mambabyte972m_L8192"
 from paper_2401_13660_amd.profile_summary import (  # noqa: E402
@@ -677,8 +674,8 @@ def main():
         "roofline": {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": traffic, "algorithmic_bytes": nbytes,
                      "scope": "whole step (all kernels of one call)"},
-        # secondary: the same step against the issue model (VALU 4.1, transcendental
-        # 8.6 SIMD-cycles per wave64 instruction; 76 + 20 per element; 2.4 GHz)
+        # secondary: the same step against the issue model (8.6 SIMD-cycles per element,
+        # 2.4 GHz)
         "alu_model": {"achieved": round(E / (ms * 1e-3) / 1e9, 2), "peak": round(ALU_PEAK_GELEMS, 1),
                       "unit": "Gelem/s", "frac": round(E / (ms * 1e-3) / 1e9 / ALU_PEAK_GELEMS, 4)},
     }

@@ -115,7 +115,7 @@ int mb_scan_fwd(const mb_scan_desc *desc,
  *
  * Where mb_scan_fwd cuts a sequence into time segments (few rows, long
  * sequences) it allocates a carry buffer on the stream: one plane of
- * batch x dim x 128 bytes per pre-pass piece (1 or 2 per segment but the last)
+ * batch x dim x 128 bytes per pre-pass piece (1, 2 or 4 per segment but the last)
  * and one for h0.  This entry point keeps that carry in a static device array of
  * 8 MiB instead: each GPU the library runs on holds its own copy until the
  * process ends.  A problem whose carry would exceed it returns MB_ERR_SHAPE
@@ -177,7 +177,8 @@ int mb_scan_fwd_states(const mb_scan_desc *desc,
  *                                  other argument; 8-byte aligned.
  *
  * Every other argument is as for mb_scan_fwd, and y and h_last are the same
- * bits as mb_scan_fwd's.  Supported: dstate 16, L a multiple of 16 below 2^25
+ * bits as mb_scan_fwd's (at L = 16, where mb_scan_fwd adds an output's terms in
+ * another order, y may differ in its last bits).  Supported: dstate 16, L a multiple of 16 below 2^25
  * (MB_ERR_UNSUPPORTED otherwise), u, delta, z, Bmat, Cmat and y 16-byte
  * aligned (MB_ERR_ALIGN otherwise).
  */

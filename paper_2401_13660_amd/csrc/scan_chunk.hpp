@@ -1,11 +1,12 @@
 // scan_chunk.hpp -- the forward selective scan for dstate = 16, one wave per chain in chunks
 // of 32 timesteps.
 //
-// For large problems that the ring kernel streams from memory more slowly: its slices of 16
-// timesteps ask for half a 128-byte line of an fp32 row at a time, and with more data than
-// the 256 MB of the Infinity Cache it reaches about 3.0 TB/s where this kernel, a line at a
-// time, reaches 3.7 ((16, 3584, 1024) fp32: 318 us and 263; with checkpoints 361 and 280;
-// bf16 with checkpoints, (16, 3584, 2048): 574 and 525).  plan::fwd has the rule.
+// For problems that the ring kernel streams from memory more slowly, and fp32 ones whose chains
+// fill the chip evenly: the ring kernel's slices of 16 timesteps ask for half a 128-byte line of
+// an fp32 row at a time, and with more data than the 256 MB of the Infinity Cache it reaches
+// about 3.0 TB/s where this kernel, a line at a time, reaches 3.7 ((16, 3584, 1024) fp32: 318 us
+// and 263; with checkpoints 361 and 280; bf16 with checkpoints, (16, 3584, 2048): 574 and 525).
+// plan::chunk_is_faster has the rule.
 //
 // Each wave works alone: it owns 8 channels of one batch element over one time segment, and
 // lane l = 8 j + q holds channel j's states 2q and 2q + 1 in VGPRs.  Per chunk it

@@ -12,9 +12,9 @@
 // wait ends: slice 0 waits for nothing, slice s for slice s - 1 only, a wave takes
 // its slices in rising order, and the waves of a workgroup are resident together.
 //
-// What bounds it: instruction issue (an exponential holds its SIMD for 8 cycles, the VALU
-// instructions beside it take 4; 172 of these and 40 of those per slice make 1,050 cycles,
-// the 972M layer takes about 1,310).  With one wave per 8 channels for a whole sequence the
+// What bounds it: instruction issue (an exponential or an MFMA holds its SIMD for 8 cycles, the
+// VALU instructions beside them take 4; 171 of these, 40 and 12 of those per slice make 1,100
+// cycles, the 972M layer takes about 1,280).  With one wave per 8 channels for a whole sequence the
 // number of waves is batch * dim / 8, so that most shapes left SIMDs with one wave or two,
 // unevenly, or paid a pre-pass that repeated every exponential to cut the sequence.  Here
 // the waves per SIMD are a free choice (4, as many as 128 VGPRs allow), and with W a

@@ -1,6 +1,5 @@
 // scan_tiled.hpp -- two kernels beside the ring kernel of the forward (dstate 16): the
-// scan of a 16-timestep sequence (the verify shape), and the pre-pass over time segments
-// with the rule that cuts them.
+// scan of a 16-timestep sequence (the verify shape), and the pre-pass over time segments.
 //
 // Each wavefront works alone: it owns 8 channels of one batch element, and lane
 // l = 8 j + q holds channel j's states 2q and 2q+1 of eq. (2) in VGPRs.  In
@@ -128,8 +127,8 @@ template <int N> __device__ __forceinline__ void lds_wait() {
 
 // The scan of a sequence of 16 timesteps (one slice per chain: the verify shape), where
 // thousands of short waves run once each.  What bounds it is the waves' set-up and first
-// memory round trip, so it uses few registers (7 waves per SIMD) and small tables: 10.5 us
-// for (32, 3584, 16), bf16 in, where the ring kernel with one wave per chain (128 VGPRs,
+// memory round trip, so it uses few registers (7 waves per SIMD) and small tables: 11.3 us
+// for (32, 3584, 16), bf16 in, in a loop (9.6 at least), where the ring kernel with one wave per chain (128 VGPRs,
 // 4 waves per SIMD) takes 12.9 us.
 // POS = true: also record the states at p.pos (p.npos > 0).
 // The grid is two-dimensional (channel groups x batch), so that a wave finds its group

@@ -5,7 +5,7 @@
  * infrastructure: the GPU test suite runs it after build() has compiled it.
  *
  * Shape: batch 2, dim 40 (the last 8-channel group has dead lanes), L 528 (the
- * tiled kernel, ending in a half chunk), dstate 16, fp32 in and out, with a
+ * ring kernel, 33 slices), dstate 16, fp32 in and out, with a
  * gate, a skip term, a timestep bias, h0 in and h_last out.
  * Exit status 0 when y and h_last meet the parity bars (2e-3 and 1e-4 under
  * |g - r| / (|r| + rms(r))), 1 otherwise, 2 on a runtime or argument error.
